@@ -174,6 +174,21 @@ hipError_t launch_gemm(int dtype, const void* A, const void* W, int M, int N, in
                        const EpiArgs& epi, hipStream_t st);
 void set_gemm_variant(int v);  // -1: by shape
 
+// The same product for few rows (gemm_few.hip) with tiles of the named size;
+// arguments checked and completed by launch_gemm, which chooses it.
+enum FewTile {
+  FEW_16x16 = 0,
+  FEW_32x32 = 1,
+  FEW_32x64 = 2,
+  FEW_64x48 = 3,
+  FEW_64x64 = 4,
+  FEW_64x96 = 5,
+  FEW_128x64 = 6,
+  FEW_TILES = 7
+};
+hipError_t launch_gemm_few(int dtype, int tile, const void* A, const void* W, int M, int N, int K,
+                           const EpiArgs& epi, hipStream_t st);
+
 // Attention of per_slot queries per slot against the seq keys of the slot:
 // q, out [n_slots * per_slot, D] (head h at columns h*dh..); k and v
 // [n_slots, H, seq, dh].

@@ -36,9 +36,10 @@
 //             Keys and values are both stored [slot, head, token, d]
 //             (whole 16-byte row chunks, also for scattered tokens).
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
-#include "common.h"
+#include "gemm_common.h"
 
 namespace marcache {
 
@@ -61,106 +62,6 @@ template <> struct Mma<float> {
   }
 };
 
-// GELU x * Phi(x) = 0.5 x (1 + erf(x / sqrt 2)), with erf from Abramowitz &
-// Stegun, Handbook of Mathematical Functions, formula 7.1.26:
-//   erf(z) = 1 - (a1 t + a2 t^2 + a3 t^3 + a4 t^4 + a5 t^5) exp(-z^2),
-//   t = 1 / (1 + p z), z >= 0, |error| <= 1.5e-7,
-// far below the bf16 rounding of the product it feeds.  With
-// q = (1 - erf(|x| / sqrt 2)) / 2:  gelu(x) = x (1 - q) for x >= 0, x q else.
-__device__ __forceinline__ float gelu_erf(float x) {
-  const float z = fabsf(x) * 0.70710678118654752440f;
-  const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f, z, 1.0f));
-  float poly = fmaf(1.061405429f, t, -1.453152027f);
-  poly = fmaf(poly, t, 1.421413741f);
-  poly = fmaf(poly, t, -0.284496736f);
-  poly = fmaf(poly, t, 0.254829592f);
-  poly *= t;
-  const float q = 0.5f * poly * __expf(-z * z);
-  return x >= 0.0f ? x * (1.0f - q) : x * q;
-}
-
-// The same GELU for outputs stored in bf16, with erf from Abramowitz &
-// Stegun formula 7.1.27:
-//   erf(z) = 1 - 1 / (1 + a1 z + a2 z^2 + a3 z^3 + a4 z^4)^4,  z >= 0,
-//   |error| <= 5e-4,
-// so with z = |x| / sqrt(2), q = (1 - erf(z)) / 2 = 1 / (2^(1/4) D)^4: the
-// polynomial is taken in |x| with its coefficients scaled by 2^(1/4) and
-// powers of 1/sqrt(2), and one reciprocal gives q.  gelu = x (1 - q) for
-// x >= 0 and x q for x < 0, which is max(x, 0) - |x| q for both signs.
-// The error in gelu is at most 2.4e-4 |x|, a sixteenth of a bf16 step.
-__device__ __forceinline__ float gelu_erf_bf16(float x) {
-  const float ax = fabsf(x);
-  float d = fmaf(0.0232216473f, ax, 0.000408675658f);  // 2^(1/4) (a4 / 4, a3 / 2^(3/2))
-  d = fmaf(d, ax, 0.136990119f);                       // 2^(1/4) a2 / 2
-  d = fmaf(d, ax, 0.234099676f);                       // 2^(1/4) a1 / 2^(1/2)
-  d = fmaf(d, ax, 1.18920712f);                        // 2^(1/4)
-  const float r = __builtin_amdgcn_rcpf(d);
-  const float r2 = r * r;
-  return fmaf(-(ax * r2), r2, fmaxf(x, 0.0f));
-}
-
-// silu(x) = x / (1 + e^-x), with the hardware exp2 and reciprocal (each
-// within a few fp32 ulps; the result is stored in bf16).  For x below
-// about -88 the exponential overflows to +inf and the quotient is -0,
-// the limit.
-__device__ __forceinline__ float silu_f(float x) {
-  return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
-}
-
-typedef __attribute__((ext_vector_type(4))) int i32x4_t;
-
-// Buffer descriptor over `bytes` bytes at `base` (raw, no stride).
-__device__ __forceinline__ i32x4_t make_rsrc(const void* base, unsigned bytes) {
-  const unsigned long p = reinterpret_cast<unsigned long>(base);
-  i32x4_t r;
-  r[0] = __builtin_amdgcn_readfirstlane(static_cast<int>(p & 0xFFFFFFFFu));
-  r[1] = __builtin_amdgcn_readfirstlane(static_cast<int>(p >> 32));
-  r[2] = __builtin_amdgcn_readfirstlane(static_cast<int>(bytes));
-  r[3] = 0x00020000;
-  return r;
-}
-
-// Sixteen bytes per lane from the buffer (byte offset voff + soff) into LDS at
-// lds_addr + 16 * lane.  Issued from asm so the compiler adds no waits of its
-// own (it would drain every load before each LDS read); the main loop waits
-// with s_waitcnt vmcnt for exactly the slice it is about to read.
-// m0 is reserved by the compiler but nothing else in these kernels uses it
-// (no LDS-DMA builtins, GWS or messages), so clobbering it here is safe.
-#pragma clang diagnostic push
-#pragma clang diagnostic ignored "-Winline-asm"
-__device__ __forceinline__ void dma16(i32x4_t rsrc, unsigned lds_addr, int voff, int soff) {
-  // the descriptor is wave-uniform; readfirstlane keeps it in SGPRs even
-  // when it was picked by a select (a no-op when it is scalar already)
-  i32x4_t r;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r[i] = __builtin_amdgcn_readfirstlane(rsrc[i]);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
-               :
-               : "s"(lds_addr), "v"(voff), "s"(r), "s"(soff)
-               : "memory", "m0");
-}
-#pragma clang diagnostic pop
-
-// Workgroup barrier that waits for this wave's LDS operations only (a
-// __syncthreads would also drain the vector-memory counter, i.e. the loads
-// already in flight for later slices).
-__device__ __forceinline__ void lds_barrier() {
-  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
-}
-
-constexpr int cmin(int a, int b) { return a < b ? a : b; }
-
-// s_waitcnt with only the vector-memory counter constrained (gfx9 encoding).
-// A wave has at most 63 such operations outstanding (issue stalls at that
-// count), so a wait for "all but the last N" with N >= 63 is a wait for all
-// but the last 63.
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-
 // ---------------------------------------------------------------------------
 // Epilogues.  The MFMA forms C^T = W A^T (weight fragment as its first
 // operand), so that acc[4 g + r] of a lane's 32 x 32 tile is output row
@@ -177,25 +78,6 @@ __device__ __forceinline__ void wait_vm() {
 // are 32-bit: the launcher keeps every output below 2 GiB.  N is a multiple
 // of 8, so a chunk is wholly inside N or wholly outside.
 // ---------------------------------------------------------------------------
-constexpr int kOob = 0x7FFFFFF0;  // an offset past every descriptor
-
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-
-__device__ __forceinline__ rsrc_t make_out(void* base, unsigned bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(base, 0, static_cast<int>(bytes), 0x00020000);
-}
-__device__ __forceinline__ void bstore16(rsrc_t r, int voff, const u32x4_t& v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, r, voff, 0, 0);
-}
-__device__ __forceinline__ u32x4_t bload16(rsrc_t r, int voff) {
-  return __builtin_amdgcn_raw_buffer_load_b128(r, voff, 0, 0);
-}
-__device__ __forceinline__ void bstore1(rsrc_t r, int voff, float x, float*) {
-  __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x), r, voff, 0, 0);
-}
-__device__ __forceinline__ void bstore1(rsrc_t r, int voff, float x, bf16_t*) {
-  __builtin_amdgcn_raw_buffer_store_b16(f2bf(x), r, voff, 0, 0);
-}
 // four consecutive output values into LDS
 __device__ __forceinline__ void lds_put4(unsigned char* p, const float* x, float*) {
   *reinterpret_cast<f32x4_t*>(p) = f32x4_t{x[0], x[1], x[2], x[3]};
@@ -241,11 +123,6 @@ __device__ __forceinline__ EpiCtx<T, KIND> make_epi(const EpiArgs& e, int M, int
     c.aux2 = make_out(e.v_copy, e.v_copy ? cache : 0u);
   }
   return c;
-}
-
-// QKV column section of global column ng: 0 query, 1 key, 2 value
-__device__ __forceinline__ int qkv_section(const EpiArgs& e, int ng) {
-  return ng >= 2 * e.d_model ? 2 : (ng >= e.d_model ? 1 : 0);
 }
 
 // Epilogue of one 32-row strip of a wave's tile: rows m_strip + 0..31,
@@ -383,28 +260,6 @@ __device__ __forceinline__ void epilogue_strip(const EpiArgs& e, const EpiCtx<T,
       if (e.v_copy) bstore16(c.aux2, ok && sec == 2 ? krow * OS : kOob, val[it]);
     }
   }
-}
-
-// Workgroup -> output tile.  Workgroups are dispatched round-robin over the
-// eight XCDs (workgroup b runs on XCD b % 8), and each XCD has its own L2.
-// Each XCD is given a contiguous range of the tile order, and that order
-// walks kGroupM row tiles before moving to the next column tile, so the
-// ~32 workgroups an XCD runs at once share 4 row tiles of A and 8 column
-// tiles of W instead of touching every row tile of A.  The map is a
-// bijection for any tile count.
-constexpr int kXcds = 8;
-constexpr int kGroupM = 4;
-__device__ __forceinline__ void tile_of(int b, int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int total = tiles_m * tiles_n;
-  const int q = total / kXcds, r = total - q * kXcds;
-  const int x = b % kXcds, l = b / kXcds;
-  const int t = x * q + min(x, r) + l;  // position in the tile order
-  const int group = kGroupM * tiles_n;
-  const int g = t / group, first_m = g * kGroupM;
-  const int gm = min(tiles_m - first_m, kGroupM);
-  const int in = t - g * group;
-  tm = first_m + in % gm;
-  tn = in / gm;
 }
 
 // Tile BM x BN, WAVES_M x WAVES_N waves, each wave (BM / WAVES_M) x
@@ -807,41 +662,86 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
   return gemm_launch<T, 256, 128, 2, 2, 3, 128, KIND>(A2, W, M2, N, K, e2, false, st);
 }
 
+// Which kernel runs a product, by the time each would take: a launch of
+// `tiles` tiles, one per CU at a time, costs its rounds times (a fixed part:
+// first loads, epilogue; plus a part per 128-byte slice of K).  The constants
+// are measured on MI355X (microseconds; fits within about 10 % over M from 10
+// to 40960, N and K from 768 to 5120, 33280 for the head's modulation):
+//  * few-row tiles (gemm_few.hip): at most one per CU; the one-wave 16 x 16
+//    and the 32 x 32 tiles share a CU, whose LDS then bounds them;
+//  * 128 x 128 tiles: at most 256 of them run one per CU with eight waves
+//    (1111 x 3080 x 768: 11.2 us, four waves 11.5), more run two per CU, 2.05 ns per tile and slice, with no
+//    hard rounds (6400 x 1024 x 4096: 61 us, against 82 in 100 tiles of 256 x
+//    256); the head's wide products on few rows persistent;
+//  * 256 x 256 tiles: 1.4 us per slice when every CU has one, 0.9 when few do
+//    (8192 x 3840 x 1280, 480 tiles: 73 us against 85 in 128 x 128 tiles, 80
+//    against 92 inside a cached step); persistent (balanced) from three rounds
+//    on, with GELU or SiLU from five.  The fp32 residual products keep two 128
+//    x 128 tiles per CU up to two rounds: alone 160 tiles of 256 x 256 are
+//    faster (8192 x 1280 x 5120: 108 us against 126), inside a step, with the
+//    residual in HBM, they are not (86 against 84 us for proj and fc2).
+// Returns kFew + tile for gemm_few.hip, else the variant.
+constexpr int kFew = 100;
+static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
+  const int cus = device_cus();
+  const bool resid = kind == EPI_RESIDUAL || kind == EPI_GATE, act = kind == EPI_GELU || kind == EPI_SILU;
+  const double s = static_cast<double>(K) * (bf16 ? 2 : 4) / 128;
+  auto tiles = [&](int bm, int bn) { return static_cast<double>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  auto rounds = [&](double t) { return std::ceil(t / cus); };
+  struct Few {
+    int bm, bn;
+    double fixed, slice, shared;  // shared: slice time per tile of a CU that several tiles share (0: they do not)
+  };
+  static const Few kBf16[FEW_TILES] = {{16, 16, 2.0, 0.084, 0.045}, {32, 32, 2.3, 0.083, 0.094}, {32, 64, 2.5, 0.124, 0},
+                                       {64, 48, 2.9, 0.149, 0},     {64, 64, 2.9, 0.169, 0},     {64, 96, 3.6, 0.205, 0},
+                                       {128, 64, 3.8, 0.254, 0}};
+  static const Few kF32[] = {{16, 16, 2.2, 0.245, 0.069}, {32, 32, 2.6, 0.255, 0.22}, {32, 64, 3.2, 0.42, 0},
+                             {64, 48, 3.8, 0.55, 0}};
+  int best = 4;
+  double cost = 1e30;
+  auto offer = [&](int v, double c) {
+    if (c < cost) {
+      cost = c;
+      best = v;
+    }
+  };
+  for (int i = 0; i < (bf16 ? FEW_TILES : 4); ++i) {
+    const Few& f = (bf16 ? kBf16 : kF32)[i];
+    const double r = rounds(tiles(f.bm, f.bn));
+    if (f.shared > 0) offer(kFew + i, f.fixed + s * std::max(f.slice, f.shared * r));
+    else if (r <= 1) offer(kFew + i, f.fixed + s * f.slice);
+  }
+  const double t128 = tiles(128, 128), t256 = tiles(256, 256);
+  if (!bf16) {
+    // fp32: the 64 x 64 tiles of the tiled kernel, then its 128 x 128 tiles
+    // (all configurations within 2 % of each other on larger products)
+    offer(6, 2.7 + s * 0.6 * std::max(1.0, tiles(64, 64) / cus));
+    offer(t128 <= cus ? 7 : 4, 6.0 + s * 1.95 * std::max(1.0, t128 / cus));
+    return best;
+  }
+  if (t128 <= cus) {
+    offer(7, 6.2 + s * 0.46);
+  } else if (resid) {
+    offer(t256 <= 2 * cus ? 4 : 8, 5.0 + t128 * (s * 2.05e-3 + 0.016));
+    return best;
+  } else {
+    offer(N >= 8192 && M <= 1024 ? 12 : 4, 5.0 + t128 * (s * 2.05e-3 + (act ? 0.006 : 0.003)));
+  }
+  if (resid) return best;
+  const double full = std::floor(t256 / cus), last = t256 - full * cus;
+  auto round256 = [&](double t) { return (act ? 13.0 : 7.0) + s * (0.85 + 0.55 * t / cus); };
+  offer(full >= (act ? 5 : 2) ? 8 : 0, full * round256(cus) + (last > 0 ? round256(last) : 0));
+  return best;
+}
+
 template <typename T, int KIND>
 static hipError_t gemm_pick(const void* A, const void* W, int M, int N, int K, const EpiArgs& e,
                             hipStream_t st) {
   const bool by_shape = g_gemm_variant < 0;
-  constexpr bool kResid = KIND == EPI_RESIDUAL || KIND == EPI_GATE;
-  constexpr bool kAct = KIND == EPI_GELU || KIND == EPI_SILU;
   int v = g_gemm_variant;
-  if (v < 0) {
-    // measured on MI355X over the MAR-L schedule's shapes (d_model 1024, M
-    // from 3200 to 40960): 128 x 128 tiles with a three-stage ring when
-    // there are at most 256 of them; 128 x 128 tiles with two workgroups per
-    // CU (early free) for the fp32 residual products and the bias products
-    // in the middle range, where they balance better; otherwise 256 x 256
-    // tiles with a two-stage ring of 128-byte slices, launched persistent
-    // once there are several tiles per CU.  Products too small to give
-    // even 128 tiles of 128 x 128 (the diffusion head's, a few hundred
-    // rows) take 64 x 64 tiles, four times as many workgroups; at most 256
-    // tiles of 128 x 128 with the fp32 residual epilogue (the cached
-    // blocks' projections at 3200 rows) run eight waves per tile; very wide
-    // products on few rows (the head's modulation product, N = 33280 on
-    // under 2048 rows) run persistent 128 x 128 tiles, two per CU.
-    const long big = static_cast<long>((M + 255) / 256) * ((N + 255) / 256);
-    const long small = static_cast<long>((M + 127) / 128) * ((N + 127) / 128);
-    if (small < 128)
-      v = 6;
-    else if (small <= 256)
-      v = kResid ? 7 : 1;
-    else if (N >= 8192 && M <= 2048)
-      v = 12;
-    else if (kResid)
-      v = big <= 512 ? 4 : 8;
-    else if (big <= 512)
-      v = kAct || big <= 256 ? 0 : 4;
-    else
-      v = big <= 1280 ? 0 : 8;
+  if (by_shape) {
+    v = choose_kernel(sizeof(T) == 2, KIND, M, N, K);
+    if (v >= kFew) return launch_gemm_few(sizeof(T) == 2 ? DT_BF16 : DT_F32, v - kFew, A, W, M, N, K, e, st);
   }
   // variants 8..15: the configurations of 0..7 launched persistent
   const bool persist = v >= 8;

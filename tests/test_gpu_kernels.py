@@ -126,6 +126,58 @@ def test_tile_variants_are_bitwise_identical(variant):
     assert torch.equal(out, ref)
 
 
+# sizes that reach every few-row tile (16 x 16, 32 x 32, 32 x 64, 64 x 48, 64 x
+# 64, 64 x 96, 128 x 64), with rows and columns that end mid-tile, and K of one
+# slice, of an odd number of slices, shorter and longer than the load rings
+FEW_ROW_SHAPES = [(1, 64, 64), (10, 1024, 320), (17, 1000, 1024), (224, 1024, 1024), (100, 776, 192),
+                  (640, 768, 3072), (509, 1288, 1216), (768, 1280, 64), (401, 2104, 640), (1023, 1528, 1536),
+                  (1600, 1032, 1024)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("M,N,K", FEW_ROW_SHAPES)
+def test_few_row_products_are_bitwise_the_tiled_ones(dtype, M, N, K):
+    """The products on few rows take kernels of their own, which sum k in the
+    order of the tiled kernel: the bits of the 128 x 128 tiles, for every
+    epilogue (bias, GELU, residual in place and scattered, key/value cache)."""
+    a = to_device(normal_rows((M, K), seed=101, dtype=dtype), dtype)
+    w = to_device(normal_rows((N, K), seed=102, std=0.05, dtype=dtype), dtype)
+    bias = to_device(normal_rows((N,), seed=103), "f32")
+    resid = to_device(normal_rows((M, N), seed=104), "f32")
+    seq = M + 3
+    idx = torch.from_numpy(random_index_sets(1, seq, M, seed=105)).to(DEV)
+    D = 64 * (K // 64)
+    wq = to_device(normal_rows((3 * D, D), seed=106, std=0.05, dtype=dtype), dtype)
+    bq = to_device(normal_rows((3 * D,), seed=107), "f32")
+
+    def products():
+        outs = [torch.full((M, N), 7.0, dtype=a.dtype, device=DEV) for _ in range(2)]
+        B.k_linear(dtype, a, w, bias, outs[0])
+        B.k_linear(dtype, a, w, bias, outs[1], gelu=True)
+        h = resid.clone()
+        B.k_linear_residual(dtype, a, w, bias, h, h)
+        y = torch.full((seq, N), 7.0, dtype=torch.float32, device=DEV)
+        copy = torch.full((M, N), 7.0, dtype=torch.float32, device=DEV)
+        B.k_linear_residual(dtype, a, w, bias, resid, y, out_idx=idx, per_slot=M, seq=seq, resid_copy=copy)
+        q = torch.full((M, D), 7.0, dtype=a.dtype, device=DEV)
+        kc, vc, v2 = (torch.full((1, D // 32, seq, 32), 7.0, dtype=a.dtype, device=DEV) for _ in range(3))
+        B.k_qkv(dtype, a, wq, bq, D, D // 32, seq, M, q_out=q, k_cache=kc, v_cache=vc, v_copy=v2, idx=idx)
+        torch.cuda.synchronize()
+        return outs + [h, y, copy, q, kc, vc, v2]
+
+    got = products()
+    try:
+        B.k_gemm_variant(4)
+        want = products()
+    finally:
+        B.k_gemm_variant(-1)
+    for g, r in zip(got, want):
+        assert torch.equal(g, r)
+    rows = np.linspace(0, M - 1, 5).astype(int)
+    ref = O.linear(_host(a)[rows], _host(w), _host(bias))
+    _close(_host(got[0])[rows], ref, dtype)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("variant", list(range(8, 16)))
 def test_persistent_workgroups_walk_several_tiles(dtype, variant):
