@@ -7,19 +7,21 @@
 // conditional, [R, 2R) unconditional), so each product of the network is
 // one launch over 2R rows:
 //   per call           gather z rows -> bf16; c = z W_z^T + b_z (fp32)
-//   per sampling step  prologue: s = silu(c + e_i) (bf16), h = x W_in^T + b_in
-//                      m = s W_ada^T + b_ada (every block's shift/scale/gate
-//                          and the final shift/scale in one product: s does
-//                          not depend on the block)
-//                      per block: u = ln(h)(1 + scale) + shift (bf16);
+//   per C sampling     s = silu(c + e_i) (bf16), C steps' rows
+//   steps              m = s W_ada^T + b_ada (every block's shift/scale/gate
+//                          and the final shift/scale, of C steps in one
+//                          product: s depends neither on the block nor on x)
+//   per sampling step  per block: u = ln(h)(1 + scale) + shift (bf16);
 //                          g = silu(u W1^T + b1) (bf16);
 //                          h = h + gate (g W2^T + b2) (fp32, in place)
-//                      out: per token, both rows' final ln-modulation and
-//                          output product, the guidance mix and the DDPM
-//                          update of the token's latent
-// The products are the block GEMM kernel with the SILU and GATE epilogues.
+//                      step: per token, both rows' final ln-modulation and
+//                          output product, the guidance mix, the DDPM update
+//                          of the token's latent x, then the next step's h =
+//                          x W_in^T + b_in and its first block's u
+// The products are the block GEMM kernels with the SILU and GATE epilogues.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <memory>
@@ -127,66 +129,31 @@ __device__ __forceinline__ float silu_h(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * x));
 }
 
-// in_w [w, T] (bf16) -> in_wt [T, w] (fp32), once at init, so that the
-// prologue reads four consecutive columns of one input component per load.
-__global__ void head_transpose_in_kernel(const bf16_t* __restrict__ in_w, int w, int T, float* __restrict__ in_wt) {
+// in_w [w, T] -> in_wt [T, w] (bf16), once at init, so that a lane reads four
+// consecutive columns of one input component per load.
+__global__ void head_transpose_in_kernel(const bf16_t* __restrict__ in_w, int w, int T, bf16_t* __restrict__ in_wt) {
   const long i = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
   if (i >= static_cast<long>(w) * T) return;
   const int col = static_cast<int>(i / T), j = static_cast<int>(i - static_cast<long>(col) * T);
-  in_wt[static_cast<long>(j) * w + col] = bf2f(in_w[i]);
+  in_wt[static_cast<long>(j) * w + col] = in_w[i];
 }
 
-// Per sampling step, one wave per row r of the 2R: s[r] = silu(c[r] + e)
-// (bf16) and h[r] = b_in + W_in x[r mod R] (fp32), with in_wt = W_in^T
-// [T, w] in fp32.  TT = T when the token width is fixed at compile time
-// (16, KL-16 latents): the token's latent then sits in registers and every
-// weight load of a column group is issued before its multiply-adds.
-template <int TT>
-__global__ __launch_bounds__(256) void head_prologue_kernel(const float* __restrict__ c,
-                                                            const float* __restrict__ e,
-                                                            const float* __restrict__ x,
-                                                            const float* __restrict__ in_wt,
-                                                            const float* __restrict__ in_b, int R, int w, int T,
-                                                            bf16_t* __restrict__ s, float* __restrict__ h) {
+// s[k 2R + r] = silu(c[r] + e[i0 - k]) (bf16) for the 2R rows of every of C
+// sampling steps i0, i0 - 1, ..., one wave per row.
+__global__ __launch_bounds__(256) void head_silu_kernel(const float* __restrict__ c, const float* __restrict__ e,
+                                                        int i0, int C, int R2, int w, bf16_t* __restrict__ s) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= 2 * R) return;
-  const float* xr = x + static_cast<long>(row >= R ? row - R : row) * T;
-  const long base = static_cast<long>(row) * w;
-  float xv[TT > 0 ? TT : 1];
-  if constexpr (TT > 0) {
-#pragma unroll
-    for (int j = 0; j < TT; j += 4) {
-      const f32x4_t q = *reinterpret_cast<const f32x4_t*>(xr + j);
-      xv[j] = q[0];
-      xv[j + 1] = q[1];
-      xv[j + 2] = q[2];
-      xv[j + 3] = q[3];
-    }
-  }
+  if (row >= C * R2) return;
+  const int k = row / R2;
+  const float* cr = c + static_cast<long>(row - k * R2) * w;
+  const float* er = e + static_cast<long>(i0 - k) * w;
+  bf16_t* sr = s + static_cast<long>(row) * w;
   for (int col = lane * 4; col < w; col += 256) {
-    const f32x4_t cv = *reinterpret_cast<const f32x4_t*>(c + base + col);
-    const f32x4_t ev = *reinterpret_cast<const f32x4_t*>(e + col);
-    f32x4_t hv = *reinterpret_cast<const f32x4_t*>(in_b + col);
-    if constexpr (TT > 0) {
-      f32x4_t wv[TT];
-#pragma unroll
-      for (int j = 0; j < TT; ++j) wv[j] = *reinterpret_cast<const f32x4_t*>(in_wt + static_cast<long>(j) * w + col);
-#pragma unroll
-      for (int j = 0; j < TT; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) hv[q] = fmaf(xv[j], wv[j][q], hv[q]);
-    } else {
-      for (int j = 0; j < T; ++j) {
-        const float xj = xr[j];
-        const f32x4_t wv = *reinterpret_cast<const f32x4_t*>(in_wt + static_cast<long>(j) * w + col);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) hv[q] = fmaf(xj, wv[q], hv[q]);
-      }
-    }
-    *reinterpret_cast<u32x2_t*>(s + base + col) =
+    const f32x4_t cv = *reinterpret_cast<const f32x4_t*>(cr + col);
+    const f32x4_t ev = *reinterpret_cast<const f32x4_t*>(er + col);
+    *reinterpret_cast<u32x2_t*>(sr + col) =
         u32x2_t{pack2bf(silu_h(cv[0] + ev[0]), silu_h(cv[1] + ev[1])), pack2bf(silu_h(cv[2] + ev[2]), silu_h(cv[3] + ev[3]))};
-    *reinterpret_cast<f32x4_t*>(h + base + col) = hv;
   }
 }
 
@@ -202,7 +169,20 @@ __device__ __forceinline__ bool group_in(int lane, int k, int w) {
 __device__ __forceinline__ float bf_lo(uint32_t a) { return __uint_as_float(a << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t a) { return __uint_as_float(a & 0xFFFF0000u); }
 
-// Row statistics (mean, 1 / sqrt(var + eps)) of a row held in v.
+// Squares of four values' distances from the mean.
+__device__ __forceinline__ float square4(const f32x4_t& v, float mean) {
+  float sq = 0.f;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float d = v[q] - mean;
+    sq = fmaf(d, d, sq);
+  }
+  return sq;
+}
+
+// Row statistics (mean, 1 / sqrt(var + eps)) of a row held in v.  Each lane
+// adds its groups' sums in group order before the sum across the wave: the
+// step kernel, whose waves hold a group each, adds in the same order.
 template <int G, bool EXACT>
 __device__ __forceinline__ void row_stats(const f32x4_t (&v)[G], int lane, int w, float eps, float& mean,
                                           float& rstd) {
@@ -214,12 +194,7 @@ __device__ __forceinline__ void row_stats(const f32x4_t (&v)[G], int lane, int w
   float sq = 0.f;
 #pragma unroll
   for (int k = 0; k < G; ++k)
-    if (group_in<G, EXACT>(lane, k, w))
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float d = v[k][q] - mean;
-        sq = fmaf(d, d, sq);
-      }
+    if (group_in<G, EXACT>(lane, k, w)) sq += square4(v[k], mean);
   rstd = __builtin_amdgcn_rsqf(wave_sum(sq) / static_cast<float>(w) + eps);
 }
 
@@ -277,11 +252,23 @@ __global__ __launch_bounds__(256) void head_lnmod_kernel(const float* __restrict
   }
 }
 
-// One workgroup of two waves per token r: wave p takes row r + p R (p = 0
-// the conditional row, 1 the unconditional one): its final ln-modulation
-// and output product.  Then the guided prediction eps = eps_u + s (eps_c -
-// eps_u) and the DDPM update of x[r] with the coefficients of sampling step
-// i and the draw xi_i[r] (not read when sigma_i = 0).
+// The end of a sampling step and the start of the next, one workgroup per
+// token r: part p of it (NWR waves, 4 columns per lane and group) has row r +
+// p R (p = 0 the conditional row, 1 the unconditional one).
+//  out   the row's final ln-modulation and output product; then the guided
+//        prediction eps = eps_u + scale (eps_c - eps_u) and the DDPM update of
+//        x[r] with the coefficients of sampling step i and the draw xi_i[r]
+//        (not read when sigma_i = 0)
+//  next  h = W_in x + b_in of the next step (x from memory without `out`)
+//  u     the first block's u = ln(h)(1 + scale) + shift from the next step's
+//        modulation rows
+// What bounds it is latency: a chain of loads, four row statistics and the
+// sum of the output components, so the row is spread over NWR waves (width
+// 1280: 5) and the weights of both products are loaded ahead of the
+// reductions.  As three kernels (one wave per row and 16 components; the
+// prologue of the next step; the first ln-modulation) it took 12.6 + 8.7 +
+// 3.6 us at 256 tokens of width 1280 on MI355X, as this one 10.2 (5 tokens of
+// width 1024: 11.4 + 5.9 + 2.3 before, 7.5 now).
 //
 // Each lane forms partial sums of all output components over its columns;
 // with T <= 16 they are summed across the wave by a reduce-scatter: four
@@ -290,91 +277,226 @@ __global__ __launch_bounds__(256) void head_lnmod_kernel(const float* __restrict
 // exchanges (distance 2, 1) complete the sum, leaving component
 // o = bits 5..2 of the lane in every lane of its group of four (a fixed
 // tree: deterministic).  Wider tokens take one wave reduction per
-// component.
-template <int G, bool EXACT>
-__global__ __launch_bounds__(128) void head_out_kernel(const float* __restrict__ h,
-                                                       const bf16_t* __restrict__ m, int ld, int shift_off,
-                                                       int scale_off, const bf16_t* __restrict__ out_w,
-                                                       const float* __restrict__ out_b, const f32x4_t* __restrict__ coef,
-                                                       int i, const float* __restrict__ xi, int R, int w, int T,
-                                                       float eps_ln, float scale, float* __restrict__ x,
-                                                       float* __restrict__ traj, float* __restrict__ eps_out) {
-  __shared__ float eps_sh[2][64];
+// component.  The waves' sums are added in wave order.
+struct StepArgs {
+  const bf16_t *out_w, *in_wt, *m_out, *m_next;  // modulation rows of this and of the next step
+  const float *out_b, *in_b, *xi;
+  const f32x4_t* coef;
+  float *h, *x, *traj, *eps_out;
+  bf16_t* u;
+  int ld, shift_out, scale_out;  // row stride of the modulation, the final shift and scale in it
+  int i, R, w, T, nwr;
+  float eps_ln, scale;
+  int out, next;
+};
+
+template <int G>
+__global__ __launch_bounds__(1024) void head_step_kernel(StepArgs a) {
+  constexpr int TB = 16;       // components reduced by the butterfly
+  constexpr int MAX_NWR = 8;   // waves per row at most
+  __shared__ float red[4][2][MAX_NWR * G][64];
+  __shared__ float part[2][MAX_NWR][64];
+  __shared__ float xs[64];
   const int lane = threadIdx.x & 63;
-  const int p = threadIdx.x >> 6;
+  const int wave = threadIdx.x >> 6;
+  const int nwr = a.nwr, w = a.w, T = a.T;
+  const int p = wave / nwr, wr = wave - p * nwr;
   const int r = blockIdx.x;
-  constexpr int TB = 16;  // components reduced by the butterfly
-  const long row = r + static_cast<long>(p) * R;
-  f32x4_t v[G];
-  load_lnmod<G, EXACT>(h + row * w, m + row * ld, shift_off, scale_off, lane, w, eps_ln, v);
-  if (T <= TB) {
-    float acc[TB];
+  const long row = r + static_cast<long>(p) * a.R;
+  int col[G];
+  bool in[G];
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-      float part = 0.f;
-      if (t < T) {
-        u32x2_t wv[G];
+  for (int g = 0; g < G; ++g) {
+    col[g] = (wr * 64 + lane) * 4 + g * nwr * 256;
+    in[g] = col[g] < w;
+  }
+  // sum over the row of each lane's group sums, in group order per lane and
+  // then across the wave; `slot`: one per reduction, so that one barrier is
+  // enough for each
+  const int groups = (w + 255) / 256;
+  auto row_sum = [&](const float (&g_sum)[G], int slot) {
 #pragma unroll
-        for (int k = 0; k < G; ++k)
-          wv[k] = group_in<G, EXACT>(lane, k, w)
-                      ? *reinterpret_cast<const u32x2_t*>(out_w + static_cast<long>(t) * w + lane * 4 + 256 * k)
-                      : u32x2_t{0u, 0u};
+    for (int g = 0; g < G; ++g) red[slot][p][g * nwr + wr][lane] = g_sum[g];
+    __syncthreads();
+    // every group's slot is read at once (a loop over the row's own count
+    // waits for LDS at each turn), those past the row count as zero
+    float q[MAX_NWR * G], t = 0.f;
 #pragma unroll
-        for (int k = 0; k < G; ++k) {
-          part = fmaf(v[k][0], bf_lo(wv[k][0]), part);
-          part = fmaf(v[k][1], bf_hi(wv[k][0]), part);
-          part = fmaf(v[k][2], bf_lo(wv[k][1]), part);
-          part = fmaf(v[k][3], bf_hi(wv[k][1]), part);
+    for (int k = 0; k < MAX_NWR * G; ++k) q[k] = red[slot][p][k][lane];
+#pragma unroll
+    for (int k = 0; k < MAX_NWR * G; ++k) t += k < groups ? q[k] : 0.f;
+    return wave_sum(t);
+  };
+  auto ln_mod = [&](f32x4_t (&v)[G], const u32x2_t (&sh)[G], const u32x2_t (&sc)[G], int slot) {
+    float sum[G], sq[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) sum[g] = (v[g][0] + v[g][1]) + (v[g][2] + v[g][3]);  // zeros past the width
+    const float mean = row_sum(sum, slot) / static_cast<float>(w);
+#pragma unroll
+    for (int g = 0; g < G; ++g) sq[g] = in[g] ? square4(v[g], mean) : 0.f;
+    const float rstd = __builtin_amdgcn_rsqf(row_sum(sq, slot + 1) / static_cast<float>(w) + a.eps_ln);
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      v[g][0] = fmaf((v[g][0] - mean) * rstd, 1.0f + bf_lo(sc[g][0]), bf_lo(sh[g][0]));
+      v[g][1] = fmaf((v[g][1] - mean) * rstd, 1.0f + bf_hi(sc[g][0]), bf_hi(sh[g][0]));
+      v[g][2] = fmaf((v[g][2] - mean) * rstd, 1.0f + bf_lo(sc[g][1]), bf_lo(sh[g][1]));
+      v[g][3] = fmaf((v[g][3] - mean) * rstd, 1.0f + bf_hi(sc[g][1]), bf_hi(sh[g][1]));
+    }
+  };
+  auto load2 = [&](const bf16_t* q, bool ok) {
+    return ok ? *reinterpret_cast<const u32x2_t*>(q) : u32x2_t{0u, 0u};
+  };
+  auto load4 = [&](const float* q, bool ok) {
+    return ok ? *reinterpret_cast<const f32x4_t*>(q) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+  };
+
+  // every load of the kernel, ahead of the first reduction
+  f32x4_t v[G], hb[G];
+  u32x2_t sh[G], sc[G], sh2[G], sc2[G], wv[TB][G], iv[TB][G];
+  const int first = min(T, TB);  // components held in registers
+  const bool updates = wave == 0 && lane < T;
+  const long at = static_cast<long>(r) * T + lane;
+  float xv = 0.f, ob = 0.f, draw = 0.f;
+  f32x4_t cf = {0.f, 0.f, 0.f, 0.f};
+  if (updates) {
+    xv = a.x[at];
+    if (a.out) {
+      cf = a.coef[a.i];
+      ob = a.out_b[lane];
+      if (a.i > 0) draw = a.xi[static_cast<long>(a.i) * a.R * T + at];  // sigma_0 = 0: entry 0 is not read
+    }
+  }
+  if (a.out) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      v[g] = load4(a.h + row * w + col[g], in[g]);
+      sh[g] = load2(a.m_out + row * a.ld + a.shift_out + col[g], in[g]);
+      sc[g] = load2(a.m_out + row * a.ld + a.scale_out + col[g], in[g]);
+    }
+  }
+  if (a.next) {
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      hb[g] = load4(a.in_b + col[g], in[g]);
+      sh2[g] = load2(a.m_next + row * a.ld + col[g], in[g] && a.m_next != nullptr);
+      sc2[g] = load2(a.m_next + row * a.ld + w + col[g], in[g] && a.m_next != nullptr);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < TB; ++t)
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      wv[t][g] = load2(a.out_w + static_cast<long>(t) * w + col[g], a.out && in[g] && t < first);
+      iv[t][g] = load2(a.in_wt + static_cast<long>(t) * w + col[g], a.next && in[g] && t < first);
+    }
+  if (a.out) {
+    ln_mod(v, sh, sc, 0);
+    if (T <= TB) {
+      float acc[TB];
+#pragma unroll
+      for (int t = 0; t < TB; ++t) {
+        float s = 0.f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+          s = fmaf(v[g][0], bf_lo(wv[t][g][0]), s);
+          s = fmaf(v[g][1], bf_hi(wv[t][g][0]), s);
+          s = fmaf(v[g][2], bf_lo(wv[t][g][1]), s);
+          s = fmaf(v[g][3], bf_hi(wv[t][g][1]), s);
+        }
+        acc[t] = s;
+      }
+      // reduce-scatter: after the exchange at distance d, lanes with that bit
+      // set hold the upper half of the remaining components
+#pragma unroll
+      for (int half = TB / 2, d = 32; half >= 1; half >>= 1, d >>= 1) {
+        const bool up = (lane & d) != 0;
+#pragma unroll
+        for (int k = 0; k < half; ++k) {
+          const float keep = up ? acc[k + half] : acc[k];
+          const float send = up ? acc[k] : acc[k + half];
+          acc[k] = keep + __shfl_xor(send, d, 64);
         }
       }
-      acc[t] = part;
-    }
-    // reduce-scatter: after the exchange at distance d, lanes with that bit
-    // set hold the upper half of the remaining components
+      float tot = acc[0];
+      tot += __shfl_xor(tot, 2, 64);
+      tot += __shfl_xor(tot, 1, 64);
+      const int comp = (((lane >> 5) & 1) << 3) | (((lane >> 4) & 1) << 2) | (((lane >> 3) & 1) << 1) | ((lane >> 2) & 1);
+      if ((lane & 3) == 0) part[p][wr][comp] = tot;
+    } else {
+      for (int t = 0; t < T; ++t) {
+        float s = 0.f;
 #pragma unroll
-    for (int half = TB / 2, d = 32; half >= 1; half >>= 1, d >>= 1) {
-      const bool up = (lane & d) != 0;
-#pragma unroll
-      for (int k = 0; k < half; ++k) {
-        const float keep = up ? acc[k + half] : acc[k];
-        const float send = up ? acc[k] : acc[k + half];
-        acc[k] = keep + __shfl_xor(send, d, 64);
+        for (int g = 0; g < G; ++g) {
+          const u32x2_t q = load2(a.out_w + static_cast<long>(t) * w + col[g], in[g]);
+          s = fmaf(v[g][0], bf_lo(q[0]), s);
+          s = fmaf(v[g][1], bf_hi(q[0]), s);
+          s = fmaf(v[g][2], bf_lo(q[1]), s);
+          s = fmaf(v[g][3], bf_hi(q[1]), s);
+        }
+        const float tot = wave_sum(s);
+        if (lane == 0) part[p][wr][t] = tot;
       }
     }
-    float tot = acc[0];
-    tot += __shfl_xor(tot, 2, 64);
-    tot += __shfl_xor(tot, 1, 64);
-    const int comp = (((lane >> 5) & 1) << 3) | (((lane >> 4) & 1) << 2) | (((lane >> 3) & 1) << 1) | ((lane >> 2) & 1);
-    if ((lane & 3) == 0 && comp < T) eps_sh[p][comp] = tot + out_b[comp];
-  } else {
-    for (int t = 0; t < T; ++t) {
-      float part = 0.f;
+    __syncthreads();
+    if (updates) {
+      float ec = 0.f, eu = 0.f, qc[MAX_NWR], qu[MAX_NWR];
 #pragma unroll
-      for (int k = 0; k < G; ++k) {
-        if (!group_in<G, EXACT>(lane, k, w)) continue;
-        const u32x2_t wv = *reinterpret_cast<const u32x2_t*>(out_w + static_cast<long>(t) * w + lane * 4 + 256 * k);
-        part = fmaf(v[k][0], bf_lo(wv[0]), part);
-        part = fmaf(v[k][1], bf_hi(wv[0]), part);
-        part = fmaf(v[k][2], bf_lo(wv[1]), part);
-        part = fmaf(v[k][3], bf_hi(wv[1]), part);
+      for (int k = 0; k < MAX_NWR; ++k) {
+        qc[k] = part[0][k][lane];
+        qu[k] = part[1][k][lane];
       }
-      const float tot = wave_sum(part) + out_b[t];
-      if (lane == t) eps_sh[p][t] = tot;
+#pragma unroll
+      for (int k = 0; k < MAX_NWR; ++k) {
+        ec += k < nwr ? qc[k] : 0.f;
+        eu += k < nwr ? qu[k] : 0.f;
+      }
+      ec += ob;
+      eu += ob;
+      const float eg = fmaf(a.scale, ec - eu, eu);
+      xv = cf[0] * fmaf(-cf[1], eg, xv);
+      if (cf[2] != 0.f) xv = fmaf(cf[2], draw, xv);
+      a.x[at] = xv;
+      if (a.traj) a.traj[at] = xv;
+      if (a.eps_out) a.eps_out[at] = eg;
     }
   }
+  if (!a.next) return;
+  if (wave == 0) xs[lane] = xv;  // zeros past T
   __syncthreads();
-  if (p == 0 && lane < T) {
-    const f32x4_t cf = coef[i];
-    const float ec = eps_sh[0][lane], eu = eps_sh[1][lane];
-    const float eg = fmaf(scale, ec - eu, eu);
-    const long at = static_cast<long>(r) * T + lane;
-    const float xv = x[at];
-    float nx = cf[0] * fmaf(-cf[1], eg, xv);
-    if (cf[2] != 0.f) nx = fmaf(cf[2], xi[static_cast<long>(i) * R * T + at], nx);
-    x[at] = nx;
-    if (traj) traj[at] = nx;
-    if (eps_out) eps_out[at] = eg;
+  float xj16[TB];
+#pragma unroll
+  for (int j = 0; j < TB; ++j) xj16[j] = xs[j];
+#pragma unroll
+  for (int j = 0; j < TB; ++j) {  // the weights past T are zeros
+    const float xj = xj16[j];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      hb[g][0] = fmaf(xj, bf_lo(iv[j][g][0]), hb[g][0]);
+      hb[g][1] = fmaf(xj, bf_hi(iv[j][g][0]), hb[g][1]);
+      hb[g][2] = fmaf(xj, bf_lo(iv[j][g][1]), hb[g][2]);
+      hb[g][3] = fmaf(xj, bf_hi(iv[j][g][1]), hb[g][3]);
+    }
   }
+  for (int j = TB; j < T; ++j) {
+    const float xj = xs[j];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const u32x2_t q = load2(a.in_wt + static_cast<long>(j) * w + col[g], in[g]);
+      hb[g][0] = fmaf(xj, bf_lo(q[0]), hb[g][0]);
+      hb[g][1] = fmaf(xj, bf_hi(q[0]), hb[g][1]);
+      hb[g][2] = fmaf(xj, bf_lo(q[1]), hb[g][2]);
+      hb[g][3] = fmaf(xj, bf_hi(q[1]), hb[g][3]);
+    }
+  }
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+    if (in[g]) *reinterpret_cast<f32x4_t*>(a.h + row * w + col[g]) = hb[g];
+  if (!a.m_next) return;
+  ln_mod(hb, sh2, sc2, 2);
+#pragma unroll
+  for (int g = 0; g < G; ++g)
+    if (in[g])
+      *reinterpret_cast<u32x2_t*>(a.u + row * w + col[g]) = u32x2_t{pack2bf(hb[g][0], hb[g][1]), pack2bf(hb[g][2], hb[g][3])};
 }
 
 }  // namespace
@@ -384,12 +506,12 @@ __global__ __launch_bounds__(128) void head_out_kernel(const float* __restrict__
 // ---------------------------------------------------------------------------
 
 // Scratch of one call: 2R rows of the network's activations (R tokens) and
-// the R latents.
+// the R latents; s and m hold the rows of `steps` sampling steps.
 struct HeadScratch {
   bf16_t* a0;  // [2R, cond_dim]
   float* c;    // [2R, w]
-  bf16_t* s;   // [2R, w]
-  bf16_t* m;   // [2R, n_mod w]
+  bf16_t* s;   // [steps 2R, w]
+  bf16_t* m;   // [steps 2R, n_mod w]
   float* h;    // [2R, w]
   bf16_t* u;   // [2R, w]
   bf16_t* g;   // [2R, w]
@@ -402,12 +524,13 @@ struct mar_head {
   // weights (matrices bf16, biases fp32)
   void *z_w, *t1_w, *t2_w, *in_w, *ada_w, *fc1_w, *fc2_w, *out_w;
   float *z_b, *t1_b, *t2_b, *in_b, *ada_b, *fc1_b, *fc2_b, *out_b;
-  float* in_wt;    // [T, w] the input product's weights, transposed, fp32
+  bf16_t* in_wt;   // [T, w] the input product's weights, transposed
   float* e;        // [steps, w] time embeddings
   f32x4_t* coef;   // [steps] DDPM coefficients
   bf16_t* phi;     // [steps, freq] (init only)
   bf16_t* t1o;     // [steps, w] (init only)
   HeadScratch sc;  // in the workspace, for up to max_rows tokens
+  size_t mod_rows; // rows that its s and m hold
 };
 
 namespace {
@@ -435,13 +558,28 @@ mar_status check_head_dims(const mar_head_dims* d) {
   return MAR_OK;
 }
 
-// Byte offsets of the scratch of a call on `rows` tokens (256-byte
-// aligned, from 0, in the order of HeadScratch's fields); returns its size.
+// Sampling steps whose modulation rows are made in one product, for calls of
+// `rows` tokens: 2048 rows' worth.  The product of one step (512 x 33280 x
+// 1280 at 256 tokens, four rounds of half-size tiles on two workgroups per CU)
+// took 50 us on MI355X; four steps' 170 us (42 a step), eight steps' 320 us,
+// which is not worth the scratch (136 MB for four at width 1280, 8 blocks).
+// At 5 tokens of width 1024 it was 11.7 us a step for 10 rows.
+constexpr size_t kModRows = 2048;
+size_t most_mod_rows(const mar_head_dims& d) {  // 32-bit offsets of the product, as for one step
+  return std::min(kModRows, ((size_t(1) << 31) - 1) / ((3 * static_cast<size_t>(d.depth) + 2) * d.width * 4));
+}
+size_t mod_steps(const mar_head_dims& d, size_t rows) {
+  return std::max<size_t>(1, std::min<size_t>(most_mod_rows(d) / (2 * rows), d.steps));
+}
+
+// Byte offsets of the scratch of a call on `rows` tokens with the modulation
+// rows of `steps` sampling steps (256-byte aligned, from 0, in the order of
+// HeadScratch's fields); returns its size.
 constexpr int kScratchBuffers = 8;
-size_t scratch_layout(const mar_head_dims& d, size_t rows, size_t* off) {
+size_t scratch_layout(const mar_head_dims& d, size_t rows, size_t mod_rows, size_t* off) {
   const size_t w = d.width, D = d.cond_dim, T = d.token_dim;
   const size_t nm = 3 * static_cast<size_t>(d.depth) + 2, R2 = 2 * rows;
-  const size_t sizes[kScratchBuffers] = {R2 * D * 2, R2 * w * 4, R2 * w * 2, R2 * nm * w * 2,
+  const size_t sizes[kScratchBuffers] = {R2 * D * 2, R2 * w * 4, mod_rows * w * 2, mod_rows * nm * w * 2,
                                          R2 * w * 4, R2 * w * 2, R2 * w * 2, rows * T * 4};
   size_t o = 0;
   for (int k = 0; k < kScratchBuffers; ++k) {
@@ -449,6 +587,13 @@ size_t scratch_layout(const mar_head_dims& d, size_t rows, size_t* off) {
     o = align_up(o + sizes[k]);
   }
   return o;
+}
+
+// Modulation rows that the workspace's scratch holds: one step's of max_rows
+// tokens, or what mod_steps() can ask for.
+size_t workspace_mod_rows(const mar_head_dims& d) {
+  const size_t all = 2 * static_cast<size_t>(d.max_rows);
+  return std::max(all, std::min(all * d.steps, most_mod_rows(d)));
 }
 
 HeadScratch scratch_at(unsigned char* base, const size_t* off) {
@@ -474,7 +619,7 @@ size_t head_layout(const mar_head_dims& d, size_t* off) {
   const size_t sizes[kTables] = {
       w * D * 2, w * F * 2, w * w * 2, w * T * 2, nm * w * w * 2, L * w * w * 2, L * w * w * 2, T * w * 2,
       w * 4, w * 4, w * 4, w * 4, nm * w * 4, L * w * 4, L * w * 4, T * 4,
-      S * w * 4, S * 16, S * F * 2, S * w * 2, T * w * 4};
+      S * w * 4, S * 16, S * F * 2, S * w * 2, T * w * 2};
   size_t o = 0;
   for (int k = 0; k < kTables; ++k) {
     off[k] = o;
@@ -482,7 +627,7 @@ size_t head_layout(const mar_head_dims& d, size_t* off) {
   }
   off[kTables] = o;
   size_t soff[kScratchBuffers];
-  return o + scratch_layout(d, static_cast<size_t>(d.max_rows), soff);
+  return o + scratch_layout(d, static_cast<size_t>(d.max_rows), workspace_mod_rows(d), soff);
 }
 constexpr int kHeadBuffers = kTables + 1;
 
@@ -495,51 +640,33 @@ hipError_t launch_rows(Kern k, int rows, hipStream_t st, Args... args) {
 
 // ln-modulation and output kernels by the groups of 4 a lane holds
 template <int G, bool EXACT>
-hipError_t lnmod_as(const mar_head* hd, const HeadScratch& sc, int off_shift, int off_scale, int rows,
+hipError_t lnmod_as(const mar_head* hd, const HeadScratch& sc, const bf16_t* m, int off_shift, int off_scale, int rows,
                     hipStream_t st) {
   return launch_rows(head_lnmod_kernel<G, EXACT>, rows, st, static_cast<const float*>(sc.h),
-                     static_cast<const bf16_t*>(sc.m), hd->n_mod * hd->d.width, off_shift, off_scale, rows,
-                     hd->d.width, hd->d.ln_eps, sc.u);
+                     m, hd->n_mod * hd->d.width, off_shift, off_scale, rows, hd->d.width, hd->d.ln_eps, sc.u);
 }
-hipError_t launch_lnmod(const mar_head* hd, const HeadScratch& sc, int off_shift, int off_scale, int rows,
+hipError_t launch_lnmod(const mar_head* hd, const HeadScratch& sc, const bf16_t* m, int off_shift, int off_scale, int rows,
                         hipStream_t st) {
   switch (hd->d.width) {
-    case 1024: return lnmod_as<4, true>(hd, sc, off_shift, off_scale, rows, st);
-    case 1280: return lnmod_as<5, true>(hd, sc, off_shift, off_scale, rows, st);
-    case 1536: return lnmod_as<6, true>(hd, sc, off_shift, off_scale, rows, st);
+    case 1024: return lnmod_as<4, true>(hd, sc, m, off_shift, off_scale, rows, st);
+    case 1280: return lnmod_as<5, true>(hd, sc, m, off_shift, off_scale, rows, st);
+    case 1536: return lnmod_as<6, true>(hd, sc, m, off_shift, off_scale, rows, st);
     default: break;
   }
   const int G = (hd->d.width + 255) / 256;
-  if (G <= 2) return lnmod_as<2, false>(hd, sc, off_shift, off_scale, rows, st);
-  if (G <= 4) return lnmod_as<4, false>(hd, sc, off_shift, off_scale, rows, st);
-  if (G <= 8) return lnmod_as<8, false>(hd, sc, off_shift, off_scale, rows, st);
-  return lnmod_as<16, false>(hd, sc, off_shift, off_scale, rows, st);
+  if (G <= 2) return lnmod_as<2, false>(hd, sc, m, off_shift, off_scale, rows, st);
+  if (G <= 4) return lnmod_as<4, false>(hd, sc, m, off_shift, off_scale, rows, st);
+  if (G <= 8) return lnmod_as<8, false>(hd, sc, m, off_shift, off_scale, rows, st);
+  return lnmod_as<16, false>(hd, sc, m, off_shift, off_scale, rows, st);
 }
-template <int G, bool EXACT>
-hipError_t out_as(const mar_head* hd, const HeadScratch& sc, int i, const float* xi, int R, float scale,
-                  float* traj, float* eps_out, hipStream_t st) {
-  const int w = hd->d.width;
-  auto kern = head_out_kernel<G, EXACT>;
-  hipLaunchKernelGGL(kern, dim3(R), dim3(128), 0, st, static_cast<const float*>(sc.h),
-                     static_cast<const bf16_t*>(sc.m), hd->n_mod * w, 3 * hd->d.depth * w, (3 * hd->d.depth + 1) * w,
-                     static_cast<const bf16_t*>(hd->out_w), static_cast<const float*>(hd->out_b),
-                     static_cast<const f32x4_t*>(hd->coef), i, xi, R, w, hd->d.token_dim, hd->d.ln_eps, scale, sc.x,
-                     traj, eps_out);
+// The step kernel: one group of 4 columns per lane up to width 2048 (8 waves
+// per row), two beyond.
+hipError_t launch_step(const mar_head* hd, StepArgs a, hipStream_t st) {
+  const int groups = a.w > 2048 ? 2 : 1;
+  a.nwr = (a.w + 256 * groups - 1) / (256 * groups);
+  auto kern = groups == 1 ? head_step_kernel<1> : head_step_kernel<2>;
+  hipLaunchKernelGGL(kern, dim3(a.R), dim3(128 * a.nwr), 0, st, a);
   return hipGetLastError();
-}
-hipError_t launch_out(const mar_head* hd, const HeadScratch& sc, int i, const float* xi, int R, float scale,
-                      float* traj, float* eps_out, hipStream_t st) {
-  switch (hd->d.width) {
-    case 1024: return out_as<4, true>(hd, sc, i, xi, R, scale, traj, eps_out, st);
-    case 1280: return out_as<5, true>(hd, sc, i, xi, R, scale, traj, eps_out, st);
-    case 1536: return out_as<6, true>(hd, sc, i, xi, R, scale, traj, eps_out, st);
-    default: break;
-  }
-  const int G = (hd->d.width + 255) / 256;
-  if (G <= 2) return out_as<2, false>(hd, sc, i, xi, R, scale, traj, eps_out, st);
-  if (G <= 4) return out_as<4, false>(hd, sc, i, xi, R, scale, traj, eps_out, st);
-  if (G <= 8) return out_as<8, false>(hd, sc, i, xi, R, scale, traj, eps_out, st);
-  return out_as<16, false>(hd, sc, i, xi, R, scale, traj, eps_out, st);
 }
 
 hipError_t fill_zero(float* p, long n, hipStream_t st) {
@@ -583,9 +710,10 @@ mar_status head_init(const mar_head_dims* dims, const mar_head_weights* W, void*
   hd->coef = reinterpret_cast<f32x4_t*>(ws + off[17]);
   hd->phi = reinterpret_cast<bf16_t*>(ws + off[18]);
   hd->t1o = reinterpret_cast<bf16_t*>(ws + off[19]);
-  hd->in_wt = reinterpret_cast<float*>(ws + off[20]);
+  hd->in_wt = reinterpret_cast<bf16_t*>(ws + off[20]);
   size_t soff[kScratchBuffers];
-  scratch_layout(d, static_cast<size_t>(d.max_rows), soff);
+  hd->mod_rows = workspace_mod_rows(d);
+  scratch_layout(d, static_cast<size_t>(d.max_rows), hd->mod_rows, soff);
   hd->sc = scratch_at(ws + off[kTables], soff);
 
   hipStream_t st = static_cast<hipStream_t>(stream);
@@ -648,8 +776,9 @@ mar_status check_sample(const mar_head* hd, const float* yc, const float* yu, in
   return MAR_OK;
 }
 
-// The sampler over R >= 1 tokens with the scratch `sc` (checked arguments).
-mar_status head_sample(const mar_head* hd, const HeadScratch& sc, const float* yc, const float* yu, int32_t y_rows,
+// The sampler over R >= 1 tokens with the scratch `sc`, whose s and m hold
+// mod_rows >= 2R rows (checked arguments).
+mar_status head_sample(const mar_head* hd, const HeadScratch& sc, size_t mod_rows, const float* yc, const float* yu, int32_t y_rows,
                        const int32_t* rc, const int32_t* ru, int32_t R, const float* x_init, const float* xi,
                        float scale, float* x_out, float* traj, float* eps_out, void* stream) {
   const mar_head_dims& d = hd->d;
@@ -668,21 +797,50 @@ mar_status head_sample(const mar_head* hd, const HeadScratch& sc, const float* y
   HEAD_HIP(gemm(sc.a0, hd->z_w, R2, w, D, ec, st), "conditioning product");
   HEAD_HIP(hipMemcpyAsync(sc.x, x_init, xbytes, hipMemcpyDeviceToDevice, st), "latent copy");
   if (traj) HEAD_HIP(hipMemcpyAsync(traj, x_init, xbytes, hipMemcpyDeviceToDevice, st), "trajectory copy");
+  StepArgs sa{};
+  sa.out_w = static_cast<const bf16_t*>(hd->out_w);
+  sa.in_wt = hd->in_wt;
+  sa.out_b = hd->out_b;
+  sa.in_b = hd->in_b;
+  sa.xi = xi;
+  sa.coef = hd->coef;
+  sa.h = sc.h;
+  sa.x = sc.x;
+  sa.u = sc.u;
+  sa.ld = nm * w;
+  sa.shift_out = 3 * d.depth * w;
+  sa.scale_out = (3 * d.depth + 1) * w;
+  sa.R = R;
+  sa.w = w;
+  sa.T = T;
+  sa.eps_ln = d.ln_eps;
+  sa.scale = scale;
+  const int batch = static_cast<int>(std::min(mod_steps(d, R), mod_rows / R2));
   for (int j = 0; j < d.steps; ++j) {
     const int i = d.steps - 1 - j;
-    HEAD_HIP(launch_rows(T == 16 ? head_prologue_kernel<16> : head_prologue_kernel<0>, R2, st,
-                         static_cast<const float*>(sc.c),
-                         static_cast<const float*>(hd->e + static_cast<long>(i) * w), static_cast<const float*>(sc.x),
-                         static_cast<const float*>(hd->in_wt), static_cast<const float*>(hd->in_b), static_cast<int>(R),
-                         w, T, sc.s, sc.h),
-             "prologue");
-    EpiArgs em{};
-    em.kind = EPI_BIAS;
-    em.bias = hd->ada_b;
-    em.out = sc.m;
-    HEAD_HIP(gemm(sc.s, hd->ada_w, R2, nm * w, w, em, st), "modulation product");
+    const int at = j % batch;  // this step's place among the steps whose modulation was made together
+    bf16_t* m = sc.m + static_cast<long>(at) * R2 * nm * w;
+    if (at == 0) {
+      const int C = std::min(batch, d.steps - j);
+      HEAD_HIP(launch_rows(head_silu_kernel, C * R2, st, static_cast<const float*>(sc.c),
+                           static_cast<const float*>(hd->e), i, C, R2, w, sc.s),
+               "conditioning");
+      EpiArgs em{};
+      em.kind = EPI_BIAS;
+      em.bias = hd->ada_b;
+      em.out = sc.m;
+      HEAD_HIP(gemm(sc.s, hd->ada_w, C * R2, nm * w, w, em, st), "modulation product");
+      if (j == 0) {
+        StepArgs first = sa;
+        first.next = 1;
+        first.m_next = m;
+        HEAD_HIP(launch_step(hd, first, st), "input product");
+      } else {
+        HEAD_HIP(launch_lnmod(hd, sc, m, 0, w, R2, st), "ln-modulation");
+      }
+    }
     for (int k = 0; k < d.depth; ++k) {
-      HEAD_HIP(launch_lnmod(hd, sc, 3 * k * w, (3 * k + 1) * w, R2, st), "ln-modulation");
+      if (k > 0) HEAD_HIP(launch_lnmod(hd, sc, m, 3 * k * w, (3 * k + 1) * w, R2, st), "ln-modulation");
       EpiArgs e1{};
       e1.kind = EPI_SILU;
       e1.bias = hd->fc1_b + static_cast<long>(k) * w;
@@ -694,14 +852,20 @@ mar_status head_sample(const mar_head* hd, const HeadScratch& sc, const float* y
       e2.bias = hd->fc2_b + static_cast<long>(k) * w;
       e2.out = sc.h;
       e2.resid = sc.h;
-      e2.gate = sc.m + static_cast<long>(3 * k + 2) * w;
+      e2.gate = m + static_cast<long>(3 * k + 2) * w;
       e2.gate_ld = nm * w;
       HEAD_HIP(gemm(sc.g, static_cast<const bf16_t*>(hd->fc2_w) + static_cast<long>(k) * w * w, R2, w, w, e2, st),
                "block second product");
     }
-    float* tj = traj ? traj + static_cast<long>(j + 1) * R * T : nullptr;
-    float* ej = eps_out ? eps_out + static_cast<long>(j) * R * T : nullptr;
-    HEAD_HIP(launch_out(hd, sc, i, xi, R, scale, tj, ej, st), "output and sampler step");
+    StepArgs step = sa;
+    step.out = 1;
+    step.next = j + 1 < d.steps;
+    step.m_out = m;
+    step.m_next = step.next && at + 1 < batch ? m + static_cast<long>(R2) * nm * w : nullptr;
+    step.i = i;
+    step.traj = traj ? traj + static_cast<long>(j + 1) * R * T : nullptr;
+    step.eps_out = eps_out ? eps_out + static_cast<long>(j) * R * T : nullptr;
+    HEAD_HIP(launch_step(hd, step, st), "output and sampler step");
   }
   HEAD_HIP(hipMemcpyAsync(x_out, sc.x, xbytes, hipMemcpyDeviceToDevice, st), "latent copy");
   return MAR_OK;
@@ -776,7 +940,7 @@ mar_status mar_head_sample(mar_head* head, const float* y_cond, const float* y_u
   mar_status s = check_sample(head, y_cond, y_uncond, y_rows, row_cond, row_uncond, rows,
                               head ? head->d.max_rows : 0, x_init, xi, scale, x_out, trajectory, eps_out);
   if (s != MAR_OK || rows == 0) return s;
-  return head_sample(head, head->sc, y_cond, y_uncond, y_rows, row_cond, row_uncond, rows, x_init, xi, scale, x_out,
+  return head_sample(head, head->sc, head->mod_rows, y_cond, y_uncond, y_rows, row_cond, row_uncond, rows, x_init, xi, scale, x_out,
                      trajectory, eps_out, stream);
 }
 
@@ -788,8 +952,13 @@ mar_status mar_head_sample_noalloc(mar_head* head, const float* y_cond, const fl
   mar_status s = check_sample(head, y_cond, y_uncond, y_rows, row_cond, row_uncond, rows, 65536, x_init, xi, scale,
                               x_out, trajectory, eps_out);
   if (s != MAR_OK || rows == 0) return s;
+  // the modulation rows of as many steps as mod_steps() asks for and the
+  // array holds next to the rest
   size_t off[kScratchBuffers];
-  const size_t need = scratch_layout(head->d, static_cast<size_t>(rows), off);
+  const size_t R2 = 2 * static_cast<size_t>(rows);
+  size_t steps = mod_steps(head->d, rows);
+  while (steps > 1 && scratch_layout(head->d, rows, steps * R2, off) > kStaticScratchBytes) --steps;
+  const size_t need = scratch_layout(head->d, rows, steps * R2, off);
   if (need > kStaticScratchBytes)
     return hfail(MAR_E_SHAPE, "%d rows need %zu bytes of scratch; the static array holds %zu", rows, need,
                  kStaticScratchBytes);
@@ -800,7 +969,7 @@ mar_status mar_head_sample_noalloc(mar_head* head, const float* y_cond, const fl
     return hfail(MAR_E_HOST, "lock failed");
   }
   if (s != MAR_OK) return s;
-  return head_sample(head, scratch_at(static_cast<unsigned char*>(base), off), y_cond, y_uncond, y_rows, row_cond,
+  return head_sample(head, scratch_at(static_cast<unsigned char*>(base), off), steps * R2, y_cond, y_uncond, y_rows, row_cond,
                      row_uncond, rows, x_init, xi, scale, x_out, trajectory, eps_out, stream);
 }
 

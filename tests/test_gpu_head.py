@@ -153,3 +153,39 @@ def test_head_one_token_and_no_tokens():
     head.sample(y, y, none, none, x0e, xie, 2.0, out)
     torch.cuda.synchronize()
     assert torch.all(out == 7.0)
+
+
+@pytest.mark.parametrize("width,token_dim,tokens,steps", [
+    (2112, 24, 5, 6),     # two column groups per lane, tokens wider than the 16 components kept in registers
+    (320, 64, 3, 5),      # the widest token; a width that fills neither its waves nor a lane group
+    (128, 16, 300, 7),    # modulation of three sampling steps at a time: steps in batches of 3, 3 and 1
+    (192, 3, 1030, 3),    # more rows than one product of several steps takes: one step at a time
+])
+def test_head_step_widths_and_batches(width, token_dim, tokens, steps):
+    """The end of one sampling step and the start of the next in one kernel,
+    with the modulation rows of several steps made together: teacher-forced."""
+    hd = HeadDims(width=width, depth=2, cond_dim=64, token_dim=token_dim, steps=steps, train_steps=60, freq_dim=64,
+                  max_rows=tokens)
+    W, zc, zu, x0, xi, x_out, traj, eps = _run(hd, tokens, tokens + 3, 3.0, seed=17)
+    np.testing.assert_array_equal(traj[0], x0)
+    np.testing.assert_array_equal(traj[-1], x_out)
+    rows = np.unique(np.linspace(0, tokens - 1, 7).astype(int))
+    _teacher_forced(hd, W, zc, zu, xi, 3.0, traj, eps, rows=rows)
+
+
+def test_head_bits_do_not_depend_on_the_batch():
+    """A token samples to the same bits whether the modulation of its steps
+    is made alone (a call whose rows fill the scratch) or for several."""
+    hd = HeadDims(width=1280, depth=1, cond_dim=64, token_dim=16, steps=5, train_steps=50, freq_dim=64, max_rows=1100)
+    W = head_weights(hd, seed=41)
+    y = to_device(normal_rows((1100, hd.cond_dim), seed=42), "f32")
+    idx = torch.arange(1100, dtype=torch.int32, device=DEV)
+    x0 = to_device(normal_rows((1100, hd.token_dim), seed=43), "f32")
+    xi = to_device(normal_rows((hd.steps, 1100, hd.token_dim), seed=44), "f32")
+    head = B.MarHead(hd, upload_head(W, hd.dtype))
+    full, part = torch.empty((1100, hd.token_dim), device=DEV), torch.empty((9, hd.token_dim), device=DEV)
+    head.sample(y, y, idx, idx, x0, xi, 3.0, full)
+    head.sample(y, y, idx[7:16].contiguous(), idx[7:16].contiguous(), x0[7:16].contiguous(),
+                xi[:, 7:16].contiguous(), 3.0, part)
+    torch.cuda.synchronize()
+    assert torch.equal(part, full[7:16])
