@@ -14,12 +14,12 @@
 // its own row and the slot's keys/values, so a query computed in a partial
 // launch is bitwise equal to the same query in a dense launch.
 //
-// fp32 path: one lane per query with scalar fp32 arithmetic.
+// fp32 path: fp32 MFMAs, 16 queries per workgroup, the keys split over its
+// waves.
 #include "common.h"
 
 namespace marcache {
 
-constexpr int kKeyTile = 64;
 constexpr float kLog2e = 1.4426950408889634f;
 
 // bf16: WAVES waves of 32 queries per workgroup; keys and values (both
@@ -280,62 +280,152 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_kernel(const bf16_t* __r
     }
 }
 
-// fp32: 64 queries per workgroup, one per lane; keys and values (the
-// values transposed on the way in) tiled in LDS.
+// fp32: 16 queries of one (slot, head) per workgroup; its four waves take the
+// 16-key tiles in turn (wave v: tiles v, v + 4, ...), each with its own online
+// softmax over its keys, and are combined through LDS at the end.  Per tile
+// and wave, with the fp32 16x16x4 MFMAs:
+//   S^T (16 keys x 16 queries) = K Q^T: lane (c, g) = (lane % 16, lane / 16)
+//     feeds key (query) c at d = g DH/4 + step, so its share of a row is DH / 4
+//     consecutive floats, loaded as they are needed;
+//   O^T (16 d x 16 queries) += V^T P^T: S^T leaves lane (c, g) with query c's
+//     keys 4 g + r, which it feeds to MFMA r; V^T follows that key order.
+// Which keys a wave takes and the order it adds them in depend on the sequence
+// length alone, so a query of a partial launch gets the bits of a dense one.
+// The products are a chain of fp32 MFMAs (32 cycles each, 32 per tile at d_head
+// 64); splitting keys over the waves shortens it fourfold and fills the chip
+// at a few hundred queries.  One lane per query with scalar arithmetic and
+// every key in turn took 297 us at 2 x 12 x 320 queries, 320 keys, d_head 64
+// on MI355X, and 297 us at 2 x 12 x 80; this takes 13 us and 9.4 us.
 template <int DH>
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float* __restrict__ Q,
-                                                      const float* __restrict__ Kc,
-                                                      const float* __restrict__ Vc,
-                                                      float* __restrict__ O, int H, int seq,
-                                                      int per_slot, float scale_log2) {
-  __shared__ float Ks[kKeyTile * DH];
-  __shared__ float Vt[DH * kKeyTile];
-  const int lane = threadIdx.x;
-  const int qblocks = (per_slot + 63) / 64;
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
+                                                       const float* __restrict__ Vc, float* __restrict__ O, int H,
+                                                       int seq, int per_slot, float scale_log2) {
+  constexpr int WAVES = 4, QB = 16, KB = 16;
+  constexpr int DL = DH / 4;    // floats of a row per lane
+  constexpr int DT = DH / 16;   // 16-row tiles of O^T
+  constexpr int OROW = DH + 1;  // row stride of the partial outputs
+  __shared__ float part_o[WAVES][QB * OROW];
+  __shared__ float part_m[WAVES][QB], part_l[WAVES][QB];
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const int c = lane & 15, g = lane >> 4;
+  const int qblocks = (per_slot + QB - 1) / QB;
   const int qb = blockIdx.x % qblocks;
   const int bh = blockIdx.x / qblocks;
   const int h = bh % H;
   const int b = bh / H;
   const int D = H * DH;
-  const int qi = qb * 64 + lane;
-  const bool q_ok = qi < per_slot;
-  const long q_row = static_cast<long>(b) * per_slot + qi;
-  float q[DH], acc[DH];
+  const long q0 = static_cast<long>(b) * per_slot + qb * QB;
+  const int nq = min(QB, per_slot - qb * QB);
+  const long head_off = (static_cast<long>(b) * H + h) * seq * DH;
+  const float* kbase = Kc + head_off + g * DL;
+  const float* vbase = Vc + head_off + c;
+
+  f32x4_t q[DL / 4];
+  {
+    const float* qr = Q + (q0 + min(c, nq - 1)) * D + h * DH + g * DL;  // rows past the end are not stored
 #pragma unroll
-  for (int d = 0; d < DH; ++d) {
-    q[d] = q_ok ? Q[q_row * D + h * DH + d] : 0.f;
-    acc[d] = 0.f;
+    for (int i = 0; i < DL / 4; ++i) q[i] = *reinterpret_cast<const f32x4_t*>(qr + 4 * i);
   }
-  const float* kbase = Kc + (static_cast<long>(b) * H + h) * seq * DH;
-  const float* vbase = Vc + (static_cast<long>(b) * H + h) * seq * DH;  // [seq][DH]
-  float m_run = -__builtin_huge_valf(), l_run = 0.f;
-  for (int key0 = 0; key0 < seq; key0 += kKeyTile) {
-    const int nk = min(kKeyTile, seq - key0);
-    __syncthreads();
-    for (int e = lane; e < nk * DH; e += 64) Ks[e] = kbase[static_cast<long>(key0) * DH + e];
-    for (int e = lane; e < DH * kKeyTile; e += 64) {
-      const int d = e / kKeyTile, j = e - d * kKeyTile;
-      Vt[e] = j < nk ? vbase[static_cast<long>(key0 + j) * DH + d] : 0.f;
-    }
-    __syncthreads();
-    for (int j = 0; j < nk; ++j) {
-      float sdot = 0.f;
+  f32x4_t acc[DT];
 #pragma unroll
-      for (int d = 0; d < DH; ++d) sdot = fmaf(q[d], Ks[j * DH + d], sdot);
-      sdot *= scale_log2;
-      const float m_new = fmaxf(m_run, sdot);
-      const float alpha = exp2f(m_run - m_new);
-      const float p = exp2f(sdot - m_new);
-      m_run = m_new;
-      l_run = l_run * alpha + p;
+  for (int t = 0; t < DT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  float m_run = -__builtin_huge_valf();
+  float l_run = 0.f;  // this lane's share of the row sum
+
+  f32x4_t k[DL / 4];
+  float v[4][DT];  // V[key 4 g + r][16 t + c]
+  auto load_keys = [&](int key0) {  // keys past the end repeat the last one
+    const float* kr = kbase + static_cast<long>(min(key0 + c, seq - 1)) * DH;
 #pragma unroll
-      for (int d = 0; d < DH; ++d) acc[d] = fmaf(p, Vt[d * kKeyTile + j], acc[d] * alpha);
+    for (int i = 0; i < DL / 4; ++i) k[i] = *reinterpret_cast<const f32x4_t*>(kr + 4 * i);
+  };
+  auto load_values = [&](int key0) {  // zeros past the end: their weights are zero
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int key = key0 + 4 * g + r;
+      const float* vr = vbase + static_cast<long>(min(key, seq - 1)) * DH;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) v[r][t] = key < seq ? vr[16 * t] : 0.f;
     }
+  };
+  if (wave * KB < seq) {
+    load_keys(wave * KB);
+    load_values(wave * KB);
   }
-  if (!q_ok) return;
-  const float inv = 1.0f / l_run;
+  for (int key0 = wave * KB; key0 < seq; key0 += WAVES * KB) {
+    f32x4_t sc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int d = 0; d < DH; ++d) O[q_row * D + h * DH + d] = acc[d] * inv;
+    for (int i = 0; i < DL / 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sc = __builtin_amdgcn_mfma_f32_16x16x4f32(k[i][j], q[i][j], sc, 0, 0, 0);
+    const int next = key0 + WAVES * KB;
+    if (next < seq) load_keys(next);
+    float tmax = -__builtin_huge_valf();
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      sc[r] = key0 + 4 * g + r < seq ? sc[r] * scale_log2 : -__builtin_huge_valf();
+      tmax = fmaxf(tmax, sc[r]);
+    }
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
+    const float m_new = fmaxf(m_run, tmax);
+    const float ref = m_new == -__builtin_huge_valf() ? 0.f : m_new;
+    const float alpha = exp2f(m_run - ref);  // 0 on the first tile
+    m_run = m_new;
+    float p[4];
+    float psum = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      p[r] = exp2f(sc[r] - ref);
+      psum += p[r];
+    }
+    l_run = fmaf(l_run, alpha, psum);
+#pragma unroll
+    for (int t = 0; t < DT; ++t) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[t][r] *= alpha;
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int t = 0; t < DT; ++t) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[r][t], p[r], acc[t], 0, 0, 0);
+    if (next < seq) load_values(next);
+  }
+  l_run += __shfl_xor(l_run, 16, 64);
+  l_run += __shfl_xor(l_run, 32, 64);
+  // acc[t][r] = O[query c][d = 16 t + 4 g + r] of this wave's keys
+#pragma unroll
+  for (int t = 0; t < DT; ++t)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) part_o[wave][c * OROW + 16 * t + 4 * g + r] = acc[t][r];
+  if (g == 0) {
+    part_m[wave][c] = m_run;
+    part_l[wave][c] = l_run;
+  }
+  __syncthreads();
+  const int row = threadIdx.x >> 4;
+  if (row >= nq) return;
+  float m = part_m[0][row];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) m = fmaxf(m, part_m[w][row]);
+  const float ref = m == -__builtin_huge_valf() ? 0.f : m;
+  float f[WAVES], l = 0.f;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) {
+    f[w] = exp2f(part_m[w][row] - ref);  // 0 for a wave without keys
+    l = fmaf(part_l[w][row], f[w], l);
+  }
+  const float inv = 1.0f / l;
+  float* out = O + (q0 + row) * D + h * DH;
+#pragma unroll
+  for (int t = 0; t < DT; ++t) {
+    const int d = 16 * t + (threadIdx.x & 15);
+    float o = 0.f;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) o = fmaf(part_o[w][row * OROW + d], f[w], o);
+    out[d] = o * inv;
+  }
 }
 
 template <int DH, int WAVES>
@@ -363,9 +453,9 @@ static hipError_t attn_launch(int dtype, const void* q, const void* k, const voi
     else
       attn_bf16_launch<DH, 2>(q, k, v, out, n_slots, H, seq, per_slot, scale_log2, st);
   } else {
-    const int qblocks = (per_slot + 63) / 64;
+    const int qblocks = (per_slot + 15) / 16;
     const long grid = static_cast<long>(n_slots) * H * qblocks;
-    hipLaunchKernelGGL(attn_f32_kernel<DH>, dim3(static_cast<unsigned>(grid)), dim3(64), 0, st,
+    hipLaunchKernelGGL(attn_f32_kernel<DH>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st,
                        static_cast<const float*>(q), static_cast<const float*>(k),
                        static_cast<const float*>(v), static_cast<float*>(out), H, seq, per_slot,
                        scale_log2);

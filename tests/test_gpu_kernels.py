@@ -350,6 +350,29 @@ def test_attention(dtype, S, dh, H, per):
     _close(out, ref, dtype)
 
 
+@pytest.mark.parametrize("S,dh,per", [(1, 16, 1), (15, 48, 15), (16, 64, 17), (17, 64, 16), (63, 80, 33), (65, 128, 1),
+                                      (130, 112, 130)])
+def test_attention_f32_key_and_query_edges(S, dh, per):
+    """fp32: sequences shorter than the four waves' key tiles, one key or
+    query past a tile, one short of it; infinite values of the last key stay
+    infinite (the padding past it adds nothing)."""
+    slots, H = 2, 3
+    q = normal_rows((slots * per, H * dh), seed=61)
+    k = normal_rows((slots, H, S, dh), seed=62)
+    v = normal_rows((slots, H, S, dh), seed=63)
+    v[1, 2, S - 1, 3] = np.inf
+    out = torch.empty((slots * per, H * dh), dtype=torch.float32, device=DEV)
+    B.k_attention("f32", to_device(q, "f32"), to_device(k, "f32"), to_device(v, "f32"), out, slots, H, S, dh, per)
+    torch.cuda.synchronize()
+    ref = np.empty((slots * per, H * dh))
+    for s in range(slots):
+        for h in range(H):
+            ref[s * per:(s + 1) * per, h * dh:(h + 1) * dh] = O.attention(
+                q[s * per:(s + 1) * per, h * dh:(h + 1) * dh], k[s, h], v[s, h])
+    assert np.all(np.isinf(ref[per:, 2 * dh + 3]))
+    _close(out, ref, "f32")
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("per", [320, 50])
 def test_attention_spiky_keys(dtype, per):
