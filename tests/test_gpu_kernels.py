@@ -476,3 +476,29 @@ def test_select_bit_exact(slots, S, n, most):
     rule = O.select_most_similar if most else O.select_least_similar
     want = np.stack([rule(s[b], n) for b in range(slots)])
     np.testing.assert_array_equal(idx.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("S", [1, 64, 511, 512, 513, 1024, 1025, 4096])
+@pytest.mark.parametrize("kind", ["equal", "ties", "range", "close"])
+def test_select_over_sizes_and_score_ranges(S, kind):
+    """Sizes around the workgroup's tokens per thread; scores that are all
+    equal, of few values, of every magnitude and sign (denormals, infinities,
+    signed zeros, NaN), and a few units in the last place apart."""
+    g = np.random.Generator(np.random.Philox(S))
+    s = {"equal": lambda: np.full((2, S), -0.25),
+         "ties": lambda: g.integers(-2, 3, (2, S)) * np.where(g.random((2, S)) < 0.5, 0.5, -0.5),
+         "range": lambda: g.standard_normal((2, S)) * np.exp2(g.integers(-1070, 1000, (2, S)).astype(np.float64)),
+         "close": lambda: 1.0 - g.integers(0, 40, (2, S)) * 2.0 ** -53}[kind]()
+    if kind == "range":
+        s[0, ::7] = g.choice([np.inf, -np.inf, np.nan, 0.0, -0.0], s[0, ::7].shape)
+    d = torch.from_numpy(np.ascontiguousarray(s, dtype=np.float64)).to(DEV)
+    for n in sorted({1, (S + 1) // 2, max(1, S - 1), S}):
+        for most in (False, True):
+            idx = torch.full((2, n), -1, dtype=torch.int32, device=DEV)
+            B.k_select(d, n, idx, most_similar=most)
+            torch.cuda.synchronize()
+            rule = O.select_most_similar if most else O.select_least_similar
+            for b in range(2):
+                np.testing.assert_array_equal(idx[b].cpu().numpy(), rule(s[b], n))
+
+
