@@ -457,6 +457,43 @@ def test_scores_bitwise(dtype, slots, H, S, dh):
     np.testing.assert_array_equal(_host(rd), v)   # the reference now holds v
 
 
+@pytest.mark.parametrize("slots", [2, 450])  # one wave per token; runs of tokens per wave
+@pytest.mark.parametrize("H,dh", [(16, 64), (1, 8), (5, 48), (16, 80), (2, 256)])
+def test_scores_bitwise_over_magnitudes(slots, H, dh):
+    """bf16 rows whose vectors fall on both sides of the range that sums
+    without rounding: single values far below or above their neighbours,
+    denormals, zeros, and rows of one magnitude; bit for bit, in the first
+    and last slots, and the reference replaced everywhere."""
+    S, D = 25, H * dh
+    g = np.random.Generator(np.random.Philox(77))
+    v, r = (g.standard_normal((slots, S, D)).astype(np.float32) for _ in range(2))
+    for s in (0, slots - 1):
+        for t in range(S):
+            kind = t % 6
+            e = np.zeros(D, np.int64)
+            if kind == 1:
+                e = g.integers(-40, 40, D)
+            elif kind == 2:
+                e[g.integers(0, D, 2)] = -17 - t
+            elif kind == 3:
+                e = np.full(D, -125)
+            elif kind == 4:
+                e = -g.integers(0, 17, D)
+            v[s, t] = np.ldexp(v[s, t], e)
+            r[s, t] = np.ldexp(r[s, t], e)
+            if kind == 5:
+                v[s, t, g.random(D) < 0.5] = 0.0
+    v, r = to_storage(v, "bf16"), to_storage(r, "bf16")
+    dev = lambda a: to_device(_cache_layout(a, H), "bf16")  # noqa: E731
+    scores = torch.empty((slots, S), dtype=torch.float64, device=DEV)
+    dv, dr = dev(v), dev(r)
+    B.k_scores("bf16", dv, dr, scores, update_ref=True)
+    torch.cuda.synchronize()
+    ends = [0, slots - 1]
+    np.testing.assert_array_equal(scores.cpu().numpy()[ends], O.cosine_scores(v[ends], r[ends]))
+    assert torch.equal(dr, dv)
+
+
 @pytest.mark.parametrize("slots,S,n", [(4, 320, 50), (2, 320, 0), (2, 320, 320), (1, 1, 1), (3, 1088, 218),
                                        (2, 4096, 1000), (5, 33, 31)])
 @pytest.mark.parametrize("most", [False, True])
