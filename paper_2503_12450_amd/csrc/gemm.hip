@@ -36,7 +36,6 @@
 //             Keys and values are both stored [slot, head, token, d]
 //             (whole 16-byte row chunks, also for scattered tokens).
 #include <algorithm>
-#include <cmath>
 #include <type_traits>
 
 #include "gemm_common.h"
@@ -683,54 +682,64 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
 // Returns kFew + tile for gemm_few.hip, else the variant.
 constexpr int kFew = 100;
 static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
-  const int cus = device_cus();
+  static const int cus = device_cus();  // of the first device used: only speed depends on it
   const bool resid = kind == EPI_RESIDUAL || kind == EPI_GATE, act = kind == EPI_GELU || kind == EPI_SILU;
-  const double s = static_cast<double>(K) * (bf16 ? 2 : 4) / 128;
-  auto tiles = [&](int bm, int bn) { return static_cast<double>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-  auto rounds = [&](double t) { return std::ceil(t / cus); };
-  struct Few {
-    int bm, bn;
-    double fixed, slice, shared;  // shared: slice time per tile of a CU that several tiles share (0: they do not)
-  };
-  static const Few kBf16[FEW_TILES] = {{16, 16, 2.0, 0.084, 0.045}, {32, 32, 2.3, 0.083, 0.094}, {32, 64, 2.5, 0.124, 0},
-                                       {64, 48, 2.9, 0.149, 0},     {64, 64, 2.9, 0.169, 0},     {64, 96, 3.6, 0.205, 0},
-                                       {128, 64, 3.8, 0.254, 0}};
-  static const Few kF32[] = {{16, 16, 2.2, 0.245, 0.069}, {32, 32, 2.6, 0.255, 0.22}, {32, 64, 3.2, 0.42, 0},
-                             {64, 48, 3.8, 0.55, 0}};
+  const float s = static_cast<float>(K) * (bf16 ? 2 : 4) / 128;
+  const float per_cu = 1.0f / cus;
+  // (tile sizes are literals below, so that a call costs the host no divisions)
+  auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
   int best = 4;
-  double cost = 1e30;
-  auto offer = [&](int v, double c) {
+  float cost = 1e30f;
+  auto offer = [&](int v, float c) {
     if (c < cost) {
       cost = c;
       best = v;
     }
   };
-  for (int i = 0; i < (bf16 ? FEW_TILES : 4); ++i) {
-    const Few& f = (bf16 ? kBf16 : kF32)[i];
-    const double r = rounds(tiles(f.bm, f.bn));
-    if (f.shared > 0) offer(kFew + i, f.fixed + s * std::max(f.slice, f.shared * r));
-    else if (r <= 1) offer(kFew + i, f.fixed + s * f.slice);
+  // few-row tiles: alone on a CU, or sharing it (`shared`: slice time per tile of the CU)
+  auto alone = [&](FewTile tile, long t, float fixed, float slice) {
+    if (t <= cus) offer(kFew + tile, fixed + s * slice);
+  };
+  auto sharing = [&](FewTile tile, long t, float fixed, float slice, float shared) {
+    offer(kFew + tile, fixed + s * std::max(slice, shared * static_cast<int>((t + cus - 1) * per_cu)));
+  };
+  const long t128 = tiles(128, 128);
+  if (t128 <= 2 * cus) {  // more are never few rows
+    if (bf16) {
+      sharing(FEW_16x16, tiles(16, 16), 2.0f, 0.084f, 0.045f);
+      sharing(FEW_32x32, tiles(32, 32), 2.3f, 0.083f, 0.094f);
+      alone(FEW_32x64, tiles(32, 64), 2.5f, 0.124f);
+      alone(FEW_64x48, tiles(64, 48), 2.9f, 0.149f);
+      alone(FEW_64x64, tiles(64, 64), 2.9f, 0.169f);
+      alone(FEW_64x96, tiles(64, 96), 3.6f, 0.205f);
+      alone(FEW_128x64, tiles(128, 64), 3.8f, 0.254f);
+    } else {
+      sharing(FEW_16x16, tiles(16, 16), 2.2f, 0.245f, 0.069f);
+      sharing(FEW_32x32, tiles(32, 32), 2.6f, 0.255f, 0.22f);
+      alone(FEW_32x64, tiles(32, 64), 3.2f, 0.42f);
+      alone(FEW_64x48, tiles(64, 48), 3.8f, 0.55f);
+    }
   }
-  const double t128 = tiles(128, 128), t256 = tiles(256, 256);
   if (!bf16) {
     // fp32: the 64 x 64 tiles of the tiled kernel, then its 128 x 128 tiles
     // (all configurations within 2 % of each other on larger products)
-    offer(6, 2.7 + s * 0.6 * std::max(1.0, tiles(64, 64) / cus));
-    offer(t128 <= cus ? 7 : 4, 6.0 + s * 1.95 * std::max(1.0, t128 / cus));
+    offer(6, 2.7f + s * 0.6f * std::max(1.0f, tiles(64, 64) * per_cu));
+    offer(t128 <= cus ? 7 : 4, 6.0f + s * 1.95f * std::max(1.0f, t128 * per_cu));
     return best;
   }
+  const long t256 = tiles(256, 256);
   if (t128 <= cus) {
-    offer(7, 6.2 + s * 0.46);
+    offer(7, 6.2f + s * 0.46f);
   } else if (resid) {
-    offer(t256 <= 2 * cus ? 4 : 8, 5.0 + t128 * (s * 2.05e-3 + 0.016));
+    offer(t256 <= 2 * cus ? 4 : 8, 5.0f + t128 * (s * 2.05e-3f + 0.016f));
     return best;
   } else {
-    offer(N >= 8192 && M <= 1024 ? 12 : 4, 5.0 + t128 * (s * 2.05e-3 + (act ? 0.006 : 0.003)));
+    offer(N >= 8192 && M <= 1024 ? 12 : 4, 5.0f + t128 * (s * 2.05e-3f + (act ? 0.006f : 0.003f)));
   }
   if (resid) return best;
-  const double full = std::floor(t256 / cus), last = t256 - full * cus;
-  auto round256 = [&](double t) { return (act ? 13.0 : 7.0) + s * (0.85 + 0.55 * t / cus); };
-  offer(full >= (act ? 5 : 2) ? 8 : 0, full * round256(cus) + (last > 0 ? round256(last) : 0));
+  const long full = t256 / cus, last = t256 - full * cus;
+  auto round256 = [&](long t) { return (act ? 13.0f : 7.0f) + s * (0.85f + 0.55f * t * per_cu); };
+  offer(full >= (act ? 5 : 2) ? 8 : 0, full * round256(cus) + (last > 0 ? round256(last) : 0.0f));
   return best;
 }
 
