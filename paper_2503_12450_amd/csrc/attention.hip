@@ -295,7 +295,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_kernel(const bf16_t* __r
 // 64); splitting keys over the waves shortens it fourfold and fills the chip
 // at a few hundred queries.  One lane per query with scalar arithmetic and
 // every key in turn took 297 us at 2 x 12 x 320 queries, 320 keys, d_head 64
-// on MI355X, and 297 us at 2 x 12 x 80; this takes 13 us and 9.4 us.
+// on MI355X, and 297 us at 2 x 12 x 80; this takes 17 us and 9.4 us.
 template <int DH>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
                                                        const float* __restrict__ Vc, float* __restrict__ O, int H,
