@@ -30,7 +30,7 @@
 #include <system_error>
 
 #include "../../include/mar_head.h"
-#include "common.h"
+#include "gemm_common.h"
 
 using namespace marcache;
 
@@ -169,33 +169,35 @@ __device__ __forceinline__ bool group_in(int lane, int k, int w) {
 __device__ __forceinline__ float bf_lo(uint32_t a) { return __uint_as_float(a << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t a) { return __uint_as_float(a & 0xFFFF0000u); }
 
-// Squares of four values' distances from the mean.
-__device__ __forceinline__ float square4(const f32x4_t& v, float mean) {
-  float sq = 0.f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const float d = v[q] - mean;
-    sq = fmaf(d, d, sq);
-  }
-  return sq;
-}
-
-// Row statistics (mean, 1 / sqrt(var + eps)) of a row held in v.  Each lane
-// adds its groups' sums in group order before the sum across the wave: the
-// step kernel, whose waves hold a group each, adds in the same order.
-template <int G, bool EXACT>
-__device__ __forceinline__ void row_stats(const f32x4_t (&v)[G], int lane, int w, float eps, float& mean,
-                                          float& rstd) {
+// Row statistics (mean, 1 / sqrt(var + eps)) of a row held in v, with in(k)
+// for the groups that this lane has, summed per lane in column order and then
+// across the wave: the step kernel's waves hold a row in the same way, so both
+// give the same bits.
+template <int G, class In>
+__device__ __forceinline__ void row_stats(const f32x4_t (&v)[G], In&& in, int w, float eps, float& mean, float& rstd) {
   float sum = 0.f;
 #pragma unroll
   for (int k = 0; k < G; ++k)
-    if (group_in<G, EXACT>(lane, k, w)) sum += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
+    if (in(k)) sum += (v[k][0] + v[k][1]) + (v[k][2] + v[k][3]);
   mean = wave_sum(sum) / static_cast<float>(w);
   float sq = 0.f;
 #pragma unroll
   for (int k = 0; k < G; ++k)
-    if (group_in<G, EXACT>(lane, k, w)) sq += square4(v[k], mean);
+    if (in(k))
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float d = v[k][q] - mean;
+        sq = fmaf(d, d, sq);
+      }
   rstd = __builtin_amdgcn_rsqf(wave_sum(sq) / static_cast<float>(w) + eps);
+}
+
+// Four values of a row: (v - mean) rstd (1 + scale) + shift.
+__device__ __forceinline__ void mod4(f32x4_t& v, float mean, float rstd, const u32x2_t& sh, const u32x2_t& sc) {
+  v[0] = fmaf((v[0] - mean) * rstd, 1.0f + bf_lo(sc[0]), bf_lo(sh[0]));
+  v[1] = fmaf((v[1] - mean) * rstd, 1.0f + bf_hi(sc[0]), bf_hi(sh[0]));
+  v[2] = fmaf((v[2] - mean) * rstd, 1.0f + bf_lo(sc[1]), bf_lo(sh[1]));
+  v[3] = fmaf((v[3] - mean) * rstd, 1.0f + bf_hi(sc[1]), bf_hi(sh[1]));
 }
 
 // v <- ln(v) (1 + scale) + shift for row `row` of h, with the shift and
@@ -220,14 +222,9 @@ __device__ __forceinline__ void load_lnmod(const float* __restrict__ hrow, const
     }
   }
   float mean, rstd;
-  row_stats<G, EXACT>(v, lane, w, eps, mean, rstd);
+  row_stats(v, [&](int k) { return group_in<G, EXACT>(lane, k, w); }, w, eps, mean, rstd);
 #pragma unroll
-  for (int k = 0; k < G; ++k) {
-    v[k][0] = fmaf((v[k][0] - mean) * rstd, 1.0f + bf_lo(sc[k][0]), bf_lo(sh[k][0]));
-    v[k][1] = fmaf((v[k][1] - mean) * rstd, 1.0f + bf_hi(sc[k][0]), bf_hi(sh[k][0]));
-    v[k][2] = fmaf((v[k][2] - mean) * rstd, 1.0f + bf_lo(sc[k][1]), bf_lo(sh[k][1]));
-    v[k][3] = fmaf((v[k][3] - mean) * rstd, 1.0f + bf_hi(sc[k][1]), bf_hi(sh[k][1]));
-  }
+  for (int k = 0; k < G; ++k) mod4(v[k], mean, rstd, sh[k], sc[k]);
 }
 
 // u[r] = ln(h[r]) (1 + scale[r]) + shift[r] (bf16), one wave per row; the
@@ -253,8 +250,9 @@ __global__ __launch_bounds__(256) void head_lnmod_kernel(const float* __restrict
 }
 
 // The end of a sampling step and the start of the next, one workgroup per
-// token r: part p of it (NWR waves, 4 columns per lane and group) has row r +
-// p R (p = 0 the conditional row, 1 the unconditional one).
+// token r: part p of it (nwr waves) has row r + p R (p = 0 the conditional
+// row, 1 the unconditional one).  A row is GT groups of 256 columns at most,
+// 4 per lane; a wave loads and stores OWN of them.
 //  out   the row's final ln-modulation and output product; then the guided
 //        prediction eps = eps_u + scale (eps_c - eps_u) and the DDPM update of
 //        x[r] with the coefficients of sampling step i and the draw xi_i[r]
@@ -262,22 +260,25 @@ __global__ __launch_bounds__(256) void head_lnmod_kernel(const float* __restrict
 //  next  h = W_in x + b_in of the next step (x from memory without `out`)
 //  u     the first block's u = ln(h)(1 + scale) + shift from the next step's
 //        modulation rows
-// What bounds it is latency: a chain of loads, four row statistics and the
-// sum of the output components, so the row is spread over NWR waves (width
-// 1280: 5) and the weights of both products are loaded ahead of the
-// reductions.  As three kernels (one wave per row and 16 components; the
-// prologue of the next step; the first ln-modulation) it took 12.6 + 8.7 +
-// 3.6 us at 256 tokens of width 1280 on MI355X, as this one 10.2 (5 tokens of
-// width 1024: 11.4 + 5.9 + 2.3 before, 7.5 now).
+// What bounds it is latency: a chain of loads, four row sums and the sum of
+// the output components.  So the loads are spread over the waves of a row and
+// meet in LDS, and every wave then holds the whole row: it forms the
+// statistics by itself (no exchange of partial sums) and a share of the output
+// components; the weights of both products are loaded ahead of the reductions.
+// As three kernels (one wave per row and 16 components; the prologue of the
+// next step; the first ln-modulation) it took 12.6 + 8.7 + 3.6 us at 256 tokens
+// of width 1280 on MI355X.  Whole calls of ten sampling steps and two blocks,
+// as three kernels and as this one: 5 tokens of width 1024 485 and 227 us, 64
+// tokens of width 1024 and 64 components 1364 and 354 us, 256 tokens of width
+// 1280 816 and 578 us.
 //
-// Each lane forms partial sums of all output components over its columns;
-// with T <= 16 they are summed across the wave by a reduce-scatter: four
-// halving exchanges (lane distance 32, 16, 8, 4) each keep half of the
-// components and add the partner's copy of that half, then two full
-// exchanges (distance 2, 1) complete the sum, leaving component
-// o = bits 5..2 of the lane in every lane of its group of four (a fixed
-// tree: deterministic).  Wider tokens take one wave reduction per
-// component.  The waves' sums are added in wave order.
+// The order of every sum is that of one wave per row: a lane's columns in
+// ascending order, then a fixed tree across the lanes.  With T <= 16 a wave
+// forms C components: halving exchanges (lane distance 32, 16, ...) each keep
+// half of the components and add the partner's copy of that half, until one is
+// left; full exchanges complete the sum, leaving component o = the lane's
+// upper bits in every lane of its group of 64 / C.  Wider tokens take one wave
+// reduction per component.
 struct StepArgs {
   const bf16_t *out_w, *in_wt, *m_out, *m_next;  // modulation rows of this and of the next step
   const float *out_b, *in_b, *xi;
@@ -290,74 +291,62 @@ struct StepArgs {
   int out, next;
 };
 
-template <int G>
-__global__ __launch_bounds__(1024) void head_step_kernel(StepArgs a) {
-  constexpr int TB = 16;       // components reduced by the butterfly
-  constexpr int MAX_NWR = 8;   // waves per row at most
-  __shared__ float red[4][2][MAX_NWR * G][64];
-  __shared__ float part[2][MAX_NWR][64];
+template <int GT, int C>
+__global__ __launch_bounds__(128 * (GT < 8 ? GT : 8)) void head_step_kernel(StepArgs a) {
+  constexpr int TB = 16;                // components held in registers
+  constexpr int OWN = GT > 8 ? 2 : 1;
+  // weights held ahead of the reductions: as many as the registers of a
+  // workgroup of this many waves take
+  constexpr bool WV = GT <= 8, IV = GT <= 6 || GT > 8;
+  __shared__ f32x4_t row_v[2][GT][64];
+  __shared__ u32x2_t row_sh[2][GT][64], row_sc[2][GT][64];
+  __shared__ float eps[2][64];
   __shared__ float xs[64];
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int nwr = a.nwr, w = a.w, T = a.T;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int nwr = OWN == 1 ? GT : a.nwr, w = a.w, T = a.T;
   const int p = wave / nwr, wr = wave - p * nwr;
   const int r = blockIdx.x;
   const long row = r + static_cast<long>(p) * a.R;
-  int col[G];
-  bool in[G];
+  const int groups = OWN == 1 ? GT : (w + 255) / 256;
+  // this lane's columns in group k of the row
+  auto in_row = [&](int k) { return (OWN == 1 && k < GT - 1) || k * 256 + lane * 4 < w; };
+  int col[OWN];
 #pragma unroll
-  for (int g = 0; g < G; ++g) {
-    col[g] = (wr * 64 + lane) * 4 + g * nwr * 256;
-    in[g] = col[g] < w;
-  }
-  // sum over the row of each lane's group sums, in group order per lane and
-  // then across the wave; `slot`: one per reduction, so that one barrier is
-  // enough for each
-  const int groups = (w + 255) / 256;
-  auto row_sum = [&](const float (&g_sum)[G], int slot) {
+  for (int g = 0; g < OWN; ++g) col[g] = (wr + g * nwr) * 256 + lane * 4;
+  // Loads through descriptors that end with the row (the matrix), of no bytes
+  // where there is nothing to load: what lies past them reads as zeros, with
+  // no branch around a load.
+  auto load2 = [&](rsrc_t q, int at) { return __builtin_amdgcn_raw_buffer_load_b64(q, at, 0, 0); };
+  auto load4 = [&](rsrc_t q, int at) { return __builtin_bit_cast(f32x4_t, bload16(q, at)); };
+  const unsigned row4 = static_cast<unsigned>(w) * 4u, row2 = static_cast<unsigned>(w) * 2u;
+  const rsrc_t r_h = make_out(a.h + row * w, row4);
+  const rsrc_t r_ow = make_out(const_cast<bf16_t*>(a.out_w), a.out ? T * row2 : 0u);
+  const rsrc_t r_iw = make_out(const_cast<bf16_t*>(a.in_wt), a.next ? T * row2 : 0u);
+  // the whole row as the waves of this part have put it into LDS
+  auto gather = [&](f32x4_t (&v)[GT]) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) red[slot][p][g * nwr + wr][lane] = g_sum[g];
-    __syncthreads();
-    // every group's slot is read at once (a loop over the row's own count
-    // waits for LDS at each turn), those past the row count as zero
-    float q[MAX_NWR * G], t = 0.f;
-#pragma unroll
-    for (int k = 0; k < MAX_NWR * G; ++k) q[k] = red[slot][p][k][lane];
-#pragma unroll
-    for (int k = 0; k < MAX_NWR * G; ++k) t += k < groups ? q[k] : 0.f;
-    return wave_sum(t);
-  };
-  auto ln_mod = [&](f32x4_t (&v)[G], const u32x2_t (&sh)[G], const u32x2_t (&sc)[G], int slot) {
-    float sum[G], sq[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) sum[g] = (v[g][0] + v[g][1]) + (v[g][2] + v[g][3]);  // zeros past the width
-    const float mean = row_sum(sum, slot) / static_cast<float>(w);
-#pragma unroll
-    for (int g = 0; g < G; ++g) sq[g] = in[g] ? square4(v[g], mean) : 0.f;
-    const float rstd = __builtin_amdgcn_rsqf(row_sum(sq, slot + 1) / static_cast<float>(w) + a.eps_ln);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      v[g][0] = fmaf((v[g][0] - mean) * rstd, 1.0f + bf_lo(sc[g][0]), bf_lo(sh[g][0]));
-      v[g][1] = fmaf((v[g][1] - mean) * rstd, 1.0f + bf_hi(sc[g][0]), bf_hi(sh[g][0]));
-      v[g][2] = fmaf((v[g][2] - mean) * rstd, 1.0f + bf_lo(sc[g][1]), bf_lo(sh[g][1]));
-      v[g][3] = fmaf((v[g][3] - mean) * rstd, 1.0f + bf_hi(sc[g][1]), bf_hi(sh[g][1]));
-    }
-  };
-  auto load2 = [&](const bf16_t* q, bool ok) {
-    return ok ? *reinterpret_cast<const u32x2_t*>(q) : u32x2_t{0u, 0u};
-  };
-  auto load4 = [&](const float* q, bool ok) {
-    return ok ? *reinterpret_cast<const f32x4_t*>(q) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k = 0; k < GT; ++k) v[k] = k < groups ? row_v[p][k][lane] : f32x4_t{0.f, 0.f, 0.f, 0.f};
   };
 
-  // every load of the kernel, ahead of the first reduction
-  f32x4_t v[G], hb[G];
-  u32x2_t sh[G], sc[G], sh2[G], sc2[G], wv[TB][G], iv[TB][G];
-  const int first = min(T, TB);  // components held in registers
+  // the loads of the kernel, ahead of the first reduction
+  const int t0 = wr * C;  // this wave's first output component, with T <= TB
+  const bool makes = a.out && t0 < T;
   const bool updates = wave == 0 && lane < T;
   const long at = static_cast<long>(r) * T + lane;
   float xv = 0.f, ob = 0.f, draw = 0.f;
-  f32x4_t cf = {0.f, 0.f, 0.f, 0.f};
+  f32x4_t cf = {0.f, 0.f, 0.f, 0.f}, hv[OWN], hb[OWN];
+  u32x2_t sh[OWN], sc[OWN], sh2[OWN], sc2[OWN], wv[WV ? C : 1][WV ? GT : 1], iv[TB][OWN];
+  if (a.out) {
+    const rsrc_t r_sh = make_out(const_cast<bf16_t*>(a.m_out) + row * a.ld + a.shift_out, row2);
+    const rsrc_t r_sc = make_out(const_cast<bf16_t*>(a.m_out) + row * a.ld + a.scale_out, row2);
+#pragma unroll
+    for (int g = 0; g < OWN; ++g) {
+      hv[g] = load4(r_h, col[g] * 4);
+      sh[g] = load2(r_sh, col[g] * 2);
+      sc[g] = load2(r_sc, col[g] * 2);
+    }
+  }
   if (updates) {
     xv = a.x[at];
     if (a.out) {
@@ -366,92 +355,98 @@ __global__ __launch_bounds__(1024) void head_step_kernel(StepArgs a) {
       if (a.i > 0) draw = a.xi[static_cast<long>(a.i) * a.R * T + at];  // sigma_0 = 0: entry 0 is not read
     }
   }
-  if (a.out) {
+  auto out_weight = [&](int c, int k) {  // component t0 + c, group k
+    return load2(r_ow, in_row(k) ? ((t0 + c) * w + k * 256 + lane * 4) * 2 : kOob);
+  };
+  if constexpr (WV) {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      v[g] = load4(a.h + row * w + col[g], in[g]);
-      sh[g] = load2(a.m_out + row * a.ld + a.shift_out + col[g], in[g]);
-      sc[g] = load2(a.m_out + row * a.ld + a.scale_out + col[g], in[g]);
+    for (int c = 0; c < C; ++c)
+#pragma unroll
+      for (int k = 0; k < GT; ++k) wv[c][k] = out_weight(c, k);
+  }
+  {
+    const rsrc_t r_b = make_out(const_cast<float*>(a.in_b), a.next ? row4 : 0u);
+    const rsrc_t r_m = make_out(const_cast<bf16_t*>(a.m_next) + row * a.ld, a.next && a.m_next ? 2 * row2 : 0u);
+#pragma unroll
+    for (int g = 0; g < OWN; ++g) {
+      hb[g] = load4(r_b, col[g] * 4);
+      sh2[g] = load2(r_m, col[g] * 2);  // (past the row only into the scale, in lanes that store nothing)
+      sc2[g] = load2(r_m, (w + col[g]) * 2);
     }
   }
-  if (a.next) {
+  auto in_weight = [&](int t, int g) { return load2(r_iw, col[g] < w ? (t * w + col[g]) * 2 : kOob); };
+  auto load_in = [&]() {
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      hb[g] = load4(a.in_b + col[g], in[g]);
-      sh2[g] = load2(a.m_next + row * a.ld + col[g], in[g] && a.m_next != nullptr);
-      sc2[g] = load2(a.m_next + row * a.ld + w + col[g], in[g] && a.m_next != nullptr);
-    }
-  }
+    for (int t = 0; t < TB; ++t)
 #pragma unroll
-  for (int t = 0; t < TB; ++t)
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      wv[t][g] = load2(a.out_w + static_cast<long>(t) * w + col[g], a.out && in[g] && t < first);
-      iv[t][g] = load2(a.in_wt + static_cast<long>(t) * w + col[g], a.next && in[g] && t < first);
-    }
+      for (int g = 0; g < OWN; ++g) iv[t][g] = in_weight(t, g);
+  };
+  if constexpr (IV) load_in();
   if (a.out) {
-    ln_mod(v, sh, sc, 0);
-    if (T <= TB) {
-      float acc[TB];
 #pragma unroll
-      for (int t = 0; t < TB; ++t) {
-        float s = 0.f;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          s = fmaf(v[g][0], bf_lo(wv[t][g][0]), s);
-          s = fmaf(v[g][1], bf_hi(wv[t][g][0]), s);
-          s = fmaf(v[g][2], bf_lo(wv[t][g][1]), s);
-          s = fmaf(v[g][3], bf_hi(wv[t][g][1]), s);
-        }
-        acc[t] = s;
-      }
-      // reduce-scatter: after the exchange at distance d, lanes with that bit
-      // set hold the upper half of the remaining components
-#pragma unroll
-      for (int half = TB / 2, d = 32; half >= 1; half >>= 1, d >>= 1) {
-        const bool up = (lane & d) != 0;
-#pragma unroll
-        for (int k = 0; k < half; ++k) {
-          const float keep = up ? acc[k + half] : acc[k];
-          const float send = up ? acc[k] : acc[k + half];
-          acc[k] = keep + __shfl_xor(send, d, 64);
-        }
-      }
-      float tot = acc[0];
-      tot += __shfl_xor(tot, 2, 64);
-      tot += __shfl_xor(tot, 1, 64);
-      const int comp = (((lane >> 5) & 1) << 3) | (((lane >> 4) & 1) << 2) | (((lane >> 3) & 1) << 1) | ((lane >> 2) & 1);
-      if ((lane & 3) == 0) part[p][wr][comp] = tot;
-    } else {
-      for (int t = 0; t < T; ++t) {
-        float s = 0.f;
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-          const u32x2_t q = load2(a.out_w + static_cast<long>(t) * w + col[g], in[g]);
-          s = fmaf(v[g][0], bf_lo(q[0]), s);
-          s = fmaf(v[g][1], bf_hi(q[0]), s);
-          s = fmaf(v[g][2], bf_lo(q[1]), s);
-          s = fmaf(v[g][3], bf_hi(q[1]), s);
-        }
-        const float tot = wave_sum(s);
-        if (lane == 0) part[p][wr][t] = tot;
-      }
+    for (int g = 0; g < OWN; ++g) {
+      row_v[p][wr + g * nwr][lane] = hv[g];
+      row_sh[p][wr + g * nwr][lane] = sh[g];
+      row_sc[p][wr + g * nwr][lane] = sc[g];
     }
     __syncthreads();
+    if (T > TB || makes) {
+      f32x4_t v[GT];
+      gather(v);
+      float mean, rstd;
+      row_stats(v, in_row, w, a.eps_ln, mean, rstd);
+#pragma unroll
+      for (int k = 0; k < GT; ++k)
+        if (k < groups) mod4(v[k], mean, rstd, row_sh[p][k][lane], row_sc[p][k][lane]);
+      auto dot = [&](float s, const f32x4_t& x, const u32x2_t& q) {
+        s = fmaf(x[0], bf_lo(q[0]), s);
+        s = fmaf(x[1], bf_hi(q[0]), s);
+        s = fmaf(x[2], bf_lo(q[1]), s);
+        return fmaf(x[3], bf_hi(q[1]), s);
+      };
+      if (T <= TB) {
+        float acc[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          float s = 0.f;
+#pragma unroll
+          for (int k = 0; k < GT; ++k)
+            if (k < groups) s = dot(s, v[k], WV ? wv[WV ? c : 0][WV ? k : 0] : out_weight(c, k));
+          acc[c] = s;
+        }
+        // reduce-scatter: after the exchange at distance d, lanes with that
+        // bit set hold the upper half of the remaining components
+#pragma unroll
+        for (int half = C / 2, d = 32; half >= 1; half >>= 1, d >>= 1) {
+          // (bit selects: written with ?: the compiler turns the picks into
+          // dynamic indexes of acc, some 50 instructions each)
+          const uint32_t up = (lane & d) != 0 ? ~0u : 0u;
+          auto pick = [&](float a, float b) {
+            return __uint_as_float((__float_as_uint(b) & up) | (__float_as_uint(a) & ~up));
+          };
+#pragma unroll
+          for (int k = 0; k < half; ++k)
+            acc[k] = pick(acc[k], acc[k + half]) + __shfl_xor(pick(acc[k + half], acc[k]), d, 64);
+        }
+        float tot = acc[0];
+#pragma unroll
+        for (int d = 32 / C; d >= 1; d >>= 1) tot += __shfl_xor(tot, d, 64);
+        if (lane % (64 / C) == 0) eps[p][t0 + lane / (64 / C)] = tot;
+      } else {
+        for (int t = wr; t < T; t += nwr) {
+          float s = 0.f;
+#pragma unroll
+          for (int k = 0; k < GT; ++k)
+            if (in_row(k)) s = dot(s, v[k], load2(r_ow, (t * w + k * 256 + lane * 4) * 2));
+          const float tot = wave_sum(s);
+          if (lane == 0) eps[p][t] = tot;
+        }
+      }
+    }
+    if constexpr (!IV) load_in();
+    __syncthreads();
     if (updates) {
-      float ec = 0.f, eu = 0.f, qc[MAX_NWR], qu[MAX_NWR];
-#pragma unroll
-      for (int k = 0; k < MAX_NWR; ++k) {
-        qc[k] = part[0][k][lane];
-        qu[k] = part[1][k][lane];
-      }
-#pragma unroll
-      for (int k = 0; k < MAX_NWR; ++k) {
-        ec += k < nwr ? qc[k] : 0.f;
-        eu += k < nwr ? qu[k] : 0.f;
-      }
-      ec += ob;
-      eu += ob;
+      const float ec = eps[0][lane] + ob, eu = eps[1][lane] + ob;
       const float eg = fmaf(a.scale, ec - eu, eu);
       xv = cf[0] * fmaf(-cf[1], eg, xv);
       if (cf[2] != 0.f) xv = fmaf(cf[2], draw, xv);
@@ -461,16 +456,14 @@ __global__ __launch_bounds__(1024) void head_step_kernel(StepArgs a) {
     }
   }
   if (!a.next) return;
+  if (!IV && !a.out) load_in();
   if (wave == 0) xs[lane] = xv;  // zeros past T
   __syncthreads();
-  float xj16[TB];
-#pragma unroll
-  for (int j = 0; j < TB; ++j) xj16[j] = xs[j];
 #pragma unroll
   for (int j = 0; j < TB; ++j) {  // the weights past T are zeros
-    const float xj = xj16[j];
+    const float xj = xs[j];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
+    for (int g = 0; g < OWN; ++g) {
       hb[g][0] = fmaf(xj, bf_lo(iv[j][g][0]), hb[g][0]);
       hb[g][1] = fmaf(xj, bf_hi(iv[j][g][0]), hb[g][1]);
       hb[g][2] = fmaf(xj, bf_lo(iv[j][g][1]), hb[g][2]);
@@ -480,8 +473,8 @@ __global__ __launch_bounds__(1024) void head_step_kernel(StepArgs a) {
   for (int j = TB; j < T; ++j) {
     const float xj = xs[j];
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const u32x2_t q = load2(a.in_wt + static_cast<long>(j) * w + col[g], in[g]);
+    for (int g = 0; g < OWN; ++g) {
+      const u32x2_t q = in_weight(j, g);
       hb[g][0] = fmaf(xj, bf_lo(q[0]), hb[g][0]);
       hb[g][1] = fmaf(xj, bf_hi(q[0]), hb[g][1]);
       hb[g][2] = fmaf(xj, bf_lo(q[1]), hb[g][2]);
@@ -489,14 +482,23 @@ __global__ __launch_bounds__(1024) void head_step_kernel(StepArgs a) {
     }
   }
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-    if (in[g]) *reinterpret_cast<f32x4_t*>(a.h + row * w + col[g]) = hb[g];
+  for (int g = 0; g < OWN; ++g) bstore16(r_h, col[g] * 4, __builtin_bit_cast(u32x4_t, hb[g]));
   if (!a.m_next) return;
-  ln_mod(hb, sh2, sc2, 2);
+  // (every wave's reads of the row before lie ahead of the barriers above)
 #pragma unroll
-  for (int g = 0; g < G; ++g)
-    if (in[g])
-      *reinterpret_cast<u32x2_t*>(a.u + row * w + col[g]) = u32x2_t{pack2bf(hb[g][0], hb[g][1]), pack2bf(hb[g][2], hb[g][3])};
+  for (int g = 0; g < OWN; ++g) row_v[p][wr + g * nwr][lane] = hb[g];
+  __syncthreads();
+  f32x4_t v[GT];
+  gather(v);
+  float mean, rstd;
+  row_stats(v, in_row, w, a.eps_ln, mean, rstd);
+  const rsrc_t r_u = make_out(a.u + row * w, row2);
+#pragma unroll
+  for (int g = 0; g < OWN; ++g) {
+    mod4(hb[g], mean, rstd, sh2[g], sc2[g]);
+    __builtin_amdgcn_raw_buffer_store_b64(u32x2_t{pack2bf(hb[g][0], hb[g][1]), pack2bf(hb[g][2], hb[g][3])}, r_u, col[g] * 2,
+                                          0, 0);
+  }
 }
 
 }  // namespace
@@ -659,12 +661,24 @@ hipError_t launch_lnmod(const mar_head* hd, const HeadScratch& sc, const bf16_t*
   if (G <= 8) return lnmod_as<8, false>(hd, sc, m, off_shift, off_scale, rows, st);
   return lnmod_as<16, false>(hd, sc, m, off_shift, off_scale, rows, st);
 }
-// The step kernel: one group of 4 columns per lane up to width 2048 (8 waves
-// per row), two beyond.
+// The step kernel: a wave per 256 columns up to width 2048, per 512 beyond,
+// and the output components over as many of a row's waves as there are (16, 8,
+// 4 or 2 each: powers of two, for the halving exchanges).
 hipError_t launch_step(const mar_head* hd, StepArgs a, hipStream_t st) {
-  const int groups = a.w > 2048 ? 2 : 1;
-  a.nwr = (a.w + 256 * groups - 1) / (256 * groups);
-  auto kern = groups == 1 ? head_step_kernel<1> : head_step_kernel<2>;
+  const int groups = (a.w + 255) / 256;
+  a.nwr = groups <= 8 ? groups : (groups + 1) / 2;
+  auto kern = head_step_kernel<16, 4>;
+  switch (groups) {
+    case 1: kern = head_step_kernel<1, 16>; break;
+    case 2: kern = head_step_kernel<2, 8>; break;
+    case 3: kern = head_step_kernel<3, 8>; break;
+    case 4: kern = head_step_kernel<4, 4>; break;
+    case 5: kern = head_step_kernel<5, 4>; break;
+    case 6: kern = head_step_kernel<6, 4>; break;
+    case 7: kern = head_step_kernel<7, 4>; break;
+    case 8: kern = head_step_kernel<8, 2>; break;
+    default: break;
+  }
   hipLaunchKernelGGL(kern, dim3(a.R), dim3(128 * a.nwr), 0, st, a);
   return hipGetLastError();
 }

@@ -14,6 +14,9 @@ latent the GPU held before that step, and
 The per-step checks keep errors from compounding over 100 steps; the final
 latents are then the trajectory's last entry.
 """
+import importlib.util
+import json
+import os
 from dataclasses import replace
 
 import numpy as np
@@ -189,3 +192,24 @@ def test_head_bits_do_not_depend_on_the_batch():
                 xi[:, 7:16].contiguous(), 3.0, part)
     torch.cuda.synchronize()
     assert torch.equal(part, full[7:16])
+
+
+def _head_bits():
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "make_head_bits.py")
+    spec = importlib.util.spec_from_file_location("make_head_bits", path)
+    mod = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(mod)
+    return mod
+
+
+HEAD_BITS = _head_bits()
+
+
+@pytest.mark.parametrize("case", HEAD_BITS.CASES, ids=HEAD_BITS.name)
+def test_head_keeps_its_bits(case):
+    """The sampled latents are those of the head with a kernel per stage and a
+    wave per row, bit for bit, whatever kernels its stages run in now."""
+    with open(HEAD_BITS.OUT) as f:
+        rows = json.load(f)[HEAD_BITS.name(case)]
+    want = np.array([[int(row[i:i + 8], 16) for i in range(0, len(row), 8)] for row in rows], dtype=np.uint32)
+    np.testing.assert_array_equal(HEAD_BITS.sample(case).view(np.uint32), want)
