@@ -295,9 +295,12 @@ template <int GT, int C>
 __global__ __launch_bounds__(128 * (GT < 8 ? GT : 8)) void head_step_kernel(StepArgs a) {
   constexpr int TB = 16;                // components held in registers
   constexpr int OWN = GT > 8 ? 2 : 1;
-  // weights held ahead of the reductions: as many as the registers of a
-  // workgroup of this many waves take
-  constexpr bool WV = GT <= 8, IV = GT <= 6 || GT > 8;
+  // Weights held ahead of the reductions: as many as the registers of a
+  // workgroup of this many waves take (128 per lane at 14 and 16 waves).  Both
+  // products' held past width 2048 spilled 46 to 173 registers to scratch
+  // memory, which the runtime may have to allocate at the first launch; ten
+  // steps of 5 tokens of width 4096 took 825 to 900 us that way, 735 this way.
+  constexpr bool WV = GT <= 8, IV = GT <= 6;
   __shared__ f32x4_t row_v[2][GT][64];
   __shared__ u32x2_t row_sh[2][GT][64], row_sc[2][GT][64];
   __shared__ float eps[2][64];

@@ -76,3 +76,23 @@ def test_noalloc_refuses_rows_past_the_array():
     assert e.value.status == B.MAR_E_SHAPE
     torch.cuda.synchronize()
     assert torch.equal(out[0], sentinel)
+
+
+@pytest.mark.parametrize("width,token_dim", [(2560, 16), (4096, 33)])
+def test_noalloc_of_wide_heads(width, token_dim):
+    """Widths past 2048 hold two column groups per wave: the first call of the
+    handle is the allocation-free one and takes no device memory."""
+    hd = HeadDims(width=width, depth=1, cond_dim=64, token_dim=token_dim, steps=4, train_steps=40, freq_dim=64,
+                  max_rows=8)
+    head = B.MarHead(hd, upload_head(head_weights(hd, seed=11), hd.dtype))
+    args = _inputs(hd, 5, 20, seed=80)
+    got, ref = _outs(hd, 5), _outs(hd, 5)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    head.sample(*args, 3.0, *got, noalloc=True)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] == free
+    head.sample(*args, 3.0, *ref)
+    torch.cuda.synchronize()
+    for a, b in zip(got, ref):
+        assert torch.equal(a, b)
