@@ -83,14 +83,24 @@ typedef struct {
   const void *fc1_w, *fc1_b, *fc2_w, *fc2_b, *out_w, *out_b;
 } mar_head_weights;
 
-/* Bytes of workspace mar_head_init needs (0 if `dims` is not supported;
- * mar_last_error() then says why). */
+/* Bytes of workspace for mar_head_init (0 if `dims` is not supported;
+ * mar_last_error() then says why).
+ *
+ * Beside the weights and one evaluation's activations it holds modulation
+ * rows (s and m above) of several sampling steps, which one product then
+ * makes together: 2 width (3 depth + 3) bytes per row, 2 rows per token and
+ * step, up to 16 steps of max_rows tokens and 2048 rows in all.  That is 16 MB
+ * for 7 tokens and 157 MB for 448 with the MAR-L head (width 1280, 8 blocks),
+ * whose weights take 147 MB.  A smaller workspace will do, down to the rows of
+ * one step of max_rows tokens (1.2 and 78 MB there): the handle makes the
+ * modulation of as many steps at a time as fit, with the same results (5
+ * tokens at one step at a time: a fifth slower). */
 size_t mar_head_workspace_bytes(const mar_head_dims* dims);
 
 /* Create a handle over a caller-allocated device workspace (256-byte
- * aligned, at least mar_head_workspace_bytes(dims) bytes): copies the
- * weights in and computes the time embedding of every sampling step on
- * `stream`.  The caller may release its weight buffers once the stream has
+ * aligned, mar_head_workspace_bytes(dims) bytes, or fewer as said there):
+ * copies the weights in and computes the time embedding of every sampling
+ * step on `stream`.  The caller may release its weight buffers once the stream has
  * passed this call; the workspace stays the library's until destroy. */
 mar_status mar_head_init(const mar_head_dims* dims, const mar_head_weights* weights, void* workspace,
                          size_t workspace_bytes, void* stream, mar_head** out);

@@ -594,11 +594,17 @@ size_t scratch_layout(const mar_head_dims& d, size_t rows, size_t mod_rows, size
   return o;
 }
 
-// Modulation rows that the workspace's scratch holds: one step's of max_rows
-// tokens, or what mod_steps() can ask for.
+// Modulation rows that a workspace of mar_head_workspace_bytes() holds: one
+// step's of max_rows tokens, or kModSteps steps' as far as mod_steps() can ask
+// for them.  All 100 steps of a small handle at once gain nothing over 16 and
+// take six times the memory: 5 tokens, 7 at most, of the width 1280 head took
+// 8163 us on MI355X with 100 steps' rows (97 MB), 8221 with 16 (16 MB), 8327
+// with 8, 10074 with one (1.2 MB); of the width 1024 head 5608, 5651, 5738,
+// 6885 us.
+constexpr size_t kModSteps = 16;
 size_t workspace_mod_rows(const mar_head_dims& d) {
   const size_t all = 2 * static_cast<size_t>(d.max_rows);
-  return std::max(all, std::min(all * d.steps, most_mod_rows(d)));
+  return std::max(all, std::min(all * std::min<size_t>(d.steps, kModSteps), most_mod_rows(d)));
 }
 
 HeadScratch scratch_at(unsigned char* base, const size_t* off) {
@@ -710,12 +716,21 @@ mar_status head_init(const mar_head_dims* dims, const mar_head_weights* W, void*
     if (!p) return hfail(MAR_E_ARG, "a weight pointer is NULL");
   if (!workspace) return hfail(MAR_E_ARG, "workspace is NULL");
   if (reinterpret_cast<uintptr_t>(workspace) % kAlign) return hfail(MAR_E_WORKSPACE, "workspace must be 256-byte aligned");
-  size_t off[kHeadBuffers];
-  const size_t need = head_layout(*dims, off);
-  if (bytes < need) return hfail(MAR_E_WORKSPACE, "workspace holds %zu bytes, %zu needed", bytes, need);
+  const mar_head_dims& d = *dims;
+  size_t off[kHeadBuffers], soff[kScratchBuffers];
+  head_layout(d, off);
+  // the modulation rows of one sampling step have to fit; of more, as many as do
+  size_t mod_rows = 2 * static_cast<size_t>(d.max_rows), most = workspace_mod_rows(d);
+  auto need = [&](size_t rows) { return off[kTables] + scratch_layout(d, static_cast<size_t>(d.max_rows), rows, soff); };
+  if (bytes < need(mod_rows))
+    return hfail(MAR_E_WORKSPACE, "workspace holds %zu bytes, %zu needed", bytes, need(mod_rows));
+  while (mod_rows < most) {
+    const size_t mid = (mod_rows + most + 1) / 2;
+    if (need(mid) <= bytes) mod_rows = mid;
+    else most = mid - 1;
+  }
   std::unique_ptr<mar_head> hd(new (std::nothrow) mar_head);
   if (!hd) return hfail(MAR_E_HOST, "out of host memory");
-  const mar_head_dims& d = *dims;
   hd->d = d;
   hd->n_mod = 3 * d.depth + 2;
   unsigned char* ws = static_cast<unsigned char*>(workspace);
@@ -728,8 +743,7 @@ mar_status head_init(const mar_head_dims* dims, const mar_head_weights* W, void*
   hd->phi = reinterpret_cast<bf16_t*>(ws + off[18]);
   hd->t1o = reinterpret_cast<bf16_t*>(ws + off[19]);
   hd->in_wt = reinterpret_cast<bf16_t*>(ws + off[20]);
-  size_t soff[kScratchBuffers];
-  hd->mod_rows = workspace_mod_rows(d);
+  hd->mod_rows = mod_rows;
   scratch_layout(d, static_cast<size_t>(d.max_rows), hd->mod_rows, soff);
   hd->sc = scratch_at(ws + off[kTables], soff);
 

@@ -194,6 +194,47 @@ def test_head_bits_do_not_depend_on_the_batch():
     assert torch.equal(part, full[7:16])
 
 
+def _one_step_bytes(hd):
+    """Workspace with the modulation rows of one sampling step, the input
+    weights' transpose in fp32: what a handle took before several steps'
+    modulation was made together."""
+    w, D, T, F, S, L, nm, R2 = (hd.width, hd.cond_dim, hd.token_dim, hd.freq_dim, hd.steps, hd.depth, hd.n_mod,
+                                2 * hd.max_rows)
+    sizes = [w * D * 2, w * F * 2, w * w * 2, w * T * 2, nm * w * w * 2, L * w * w * 2, L * w * w * 2, T * w * 2,
+             w * 4, w * 4, w * 4, w * 4, nm * w * 4, L * w * 4, L * w * 4, T * 4,
+             S * w * 4, S * 16, S * F * 2, S * w * 2, T * w * 4,
+             R2 * D * 2, R2 * w * 4, R2 * w * 2, R2 * nm * w * 2, R2 * w * 4, R2 * w * 2, R2 * w * 2, R2 // 2 * T * 4]
+    return sum((s + 255) // 256 * 256 for s in sizes)
+
+
+@pytest.mark.parametrize("steps_held", [1, 2, 7])
+def test_head_takes_a_workspace_of_fewer_steps(monkeypatch, steps_held):
+    """A workspace that holds the modulation rows of one step, or of some, is
+    taken and samples to the same bits; one that does not hold one step's is
+    refused."""
+    hd = HeadDims(width=320, depth=2, cond_dim=64, token_dim=16, steps=9, train_steps=90, freq_dim=64, max_rows=20)
+    W = upload_head(head_weights(hd, seed=71), hd.dtype)
+    y = to_device(normal_rows((20, hd.cond_dim), seed=72), "f32")
+    idx = torch.arange(20, dtype=torch.int32, device=DEV)
+    x0 = to_device(normal_rows((20, hd.token_dim), seed=73), "f32")
+    xi = to_device(normal_rows((hd.steps, 20, hd.token_dim), seed=74), "f32")
+    full, got = torch.empty((20, hd.token_dim), device=DEV), torch.empty((20, hd.token_dim), device=DEV)
+    B.MarHead(hd, W).sample(y, y, idx, idx, x0, xi, 3.0, full)
+    row = 2 * hd.width * (hd.n_mod + 1)
+    nbytes = _one_step_bytes(hd) + (steps_held - 1) * 2 * hd.max_rows * row
+    assert nbytes < B.head_workspace_bytes(hd)
+    with monkeypatch.context() as m:
+        m.setattr(B, "head_workspace_bytes", lambda _: nbytes)
+        head = B.MarHead(hd, W)
+        m.setattr(B, "head_workspace_bytes", lambda _: _one_step_bytes(hd) - 2 * hd.token_dim * hd.width - row)
+        with pytest.raises(B.MarError) as e:
+            B.MarHead(hd, W)
+    assert e.value.status == B.MAR_E_WORKSPACE
+    head.sample(y, y, idx, idx, x0, xi, 3.0, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got, full)
+
+
 def _head_bits():
     path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "make_head_bits.py")
     spec = importlib.util.spec_from_file_location("make_head_bits", path)
