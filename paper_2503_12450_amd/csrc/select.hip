@@ -213,24 +213,25 @@ __device__ __forceinline__ int block_scan(int v, int* sums, int& total) {
   return before + inc - v;
 }
 
-// A radix selection, one workgroup of 512 threads per slot, each owning PER
-// consecutive tokens as 64-bit keys in score order.  The key range's common
+// A radix selection, one workgroup per slot, whose threads own PER consecutive
+// tokens each as 64-bit keys in score order.  The key range's common
 // leading bits are skipped; then each pass counts the candidates (the keys
 // that still agree with the n-th smallest) by their next 8 bits and keeps the
 // bin that holds it, until that bin is wanted whole or no bits are left (equal
 // scores: lowest index first).  What bounds it is the latency of a pass (three
 // barriers, about 0.7 us) and a launch; two or three passes are usual.
 // Ranking every token against every other took 21 us at 320 tokens and 150 us
-// at 1088 on MI355X.
-constexpr int kSelectThreads = 512;
-template <int PER>
-__global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __restrict__ scores, int seq, int n,
+// at 1088 on MI355X.  A workgroup has no more waves than its slot fills:
+// with 512 threads for every length 4096 slots of 16 tokens took 22 us and 1024
+// of 32 8.3 us (ranked 12.4 and 5.5), now 5.3 and 4.1.
+template <int THREADS, int PER>
+__global__ __launch_bounds__(THREADS) void select_kernel(const double* __restrict__ scores, int seq, int n,
                                                                 int largest, int32_t* __restrict__ idx) {
   typedef unsigned long long u64;
-  __shared__ u64 lohi[2][kSelectThreads / 64];
+  __shared__ u64 lohi[2][THREADS / 64];
   __shared__ int hist[256];
   __shared__ int found[3];  // digit, candidates before it, candidates in it
-  __shared__ int sums[2][kSelectThreads / 64];
+  __shared__ int sums[2][THREADS / 64];
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const double* s = scores + static_cast<long>(b) * seq;
   const int t0 = tid * PER;
@@ -260,7 +261,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __
   }
   __syncthreads();
 #pragma unroll
-  for (int w = 0; w < kSelectThreads / 64; ++w) {
+  for (int w = 0; w < THREADS / 64; ++w) {
     lo_k = min(lo_k, lohi[0][w]);
     hi_k = max(hi_k, lohi[1][w]);
   }
@@ -279,7 +280,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __
   auto above = [&](u64 k) { return bit < 64 ? k >> bit : u64(0); };
   while (bit > 0 && need < cand) {
     const int width = min(8, bit), next = bit - width;
-    for (int i = tid; i < 256; i += kSelectThreads) hist[i] = 0;
+    for (int i = tid; i < 256; i += THREADS) hist[i] = 0;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < PER; ++i)
@@ -329,12 +330,12 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __
     ties |= (own && a == prefix ? 1u : 0u) << i;
   }
   int total;
-  int left = need - block_scan<kSelectThreads>(__popc(ties), sums[0], total);
+  int left = need - block_scan<THREADS>(__popc(ties), sums[0], total);
   for (; ties != 0 && left > 0; --left) {
     chosen |= ties & -ties;
     ties &= ties - 1;
   }
-  int to = block_scan<kSelectThreads>(__popc(chosen), sums[1], total);
+  int to = block_scan<THREADS>(__popc(chosen), sums[1], total);
   int32_t* out = idx + static_cast<long>(b) * n;
 #pragma unroll
   for (int i = 0; i < PER; ++i)
@@ -381,12 +382,16 @@ hipError_t launch_scores(int dtype, const void* v_cur, void* v_ref, int n_slots,
 hipError_t launch_select(const double* scores, int n_slots, int seq, int n, bool largest, int32_t* idx,
                          hipStream_t st) {
   if (n_slots == 0 || n == 0) return hipSuccess;
-  auto kern = seq <= kSelectThreads       ? select_kernel<1>
-              : seq <= 2 * kSelectThreads ? select_kernel<2>
-              : seq <= 4 * kSelectThreads ? select_kernel<4>
-                                          : select_kernel<8>;
-  if (seq > 8 * kSelectThreads) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3(n_slots), dim3(kSelectThreads), 0, st, scores, seq, n, largest ? 1 : 0, idx);
+  auto kern = seq <= 64     ? select_kernel<64, 1>
+              : seq <= 128  ? select_kernel<128, 1>
+              : seq <= 256  ? select_kernel<256, 1>
+              : seq <= 512  ? select_kernel<512, 1>
+              : seq <= 1024 ? select_kernel<512, 2>
+              : seq <= 2048 ? select_kernel<512, 4>
+                            : select_kernel<512, 8>;
+  const int threads = seq <= 64 ? 64 : seq <= 128 ? 128 : seq <= 256 ? 256 : 512;
+  if (seq > 4096) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kern, dim3(n_slots), dim3(threads), 0, st, scores, seq, n, largest ? 1 : 0, idx);
   return hipGetLastError();
 }
 

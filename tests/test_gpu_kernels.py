@@ -539,3 +539,20 @@ def test_select_over_sizes_and_score_ranges(S, kind):
                 np.testing.assert_array_equal(idx[b].cpu().numpy(), rule(s[b], n))
 
 
+@pytest.mark.parametrize("S", [1, 63, 64, 65, 128, 129, 256, 257, 1024, 1025, 2048, 2049, 4096])
+def test_select_of_many_sequences(S):
+    """Several hundred sequences per launch at the edges of every workgroup
+    size and of the tokens per thread; scores a few units in the last place
+    apart, with one far below, so that a selection takes up to eight passes."""
+    slots = 400
+    g = np.random.Generator(np.random.Philox(1000 + S))
+    s = 1.0 - g.integers(0, 3 * S, (slots, S)) * 2.0 ** -53
+    s[np.arange(slots), g.integers(0, S, slots)] = -1e300
+    d = torch.from_numpy(s).to(DEV)
+    n = max(1, (2 * S) // 5)
+    for most in (False, True):
+        idx = torch.full((slots, n), -1, dtype=torch.int32, device=DEV)
+        B.k_select(d, n, idx, most_similar=most)
+        torch.cuda.synchronize()
+        rule = O.select_most_similar if most else O.select_least_similar
+        np.testing.assert_array_equal(idx.cpu().numpy(), np.stack([rule(s[b], n) for b in range(slots)]))
