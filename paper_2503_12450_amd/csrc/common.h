@@ -110,6 +110,11 @@ __device__ __forceinline__ double wave_sum(double v) {
   return v;
 }
 
+// Workgroups of one launch at most: the runtime refuses a launch of 2^32
+// threads or more, so a grid that depends on sizes of the caller's choice is
+// cut into launches of this many workgroups (of up to 512 threads).
+constexpr long kMaxGrid = 1l << 22;
+
 // The thread-local message behind mar_last_error(): cleared at the start of
 // every C entry point, set by a failing one (never allocates).
 void abi_clear_error();

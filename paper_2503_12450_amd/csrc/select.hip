@@ -17,6 +17,8 @@
 //   smallest in the strict total order (score, index).  The opposite rule (the
 //   n largest scores: Table 3's strategy that caches the least similar tokens)
 //   ranks by (-score, index), NaN again last.
+#include <algorithm>
+
 #include "common.h"
 
 namespace marcache {
@@ -391,8 +393,13 @@ hipError_t launch_select(const double* scores, int n_slots, int seq, int n, bool
                             : select_kernel<512, 8>;
   const int threads = seq <= 64 ? 64 : seq <= 128 ? 128 : seq <= 256 ? 256 : 512;
   if (seq > 4096) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(kern, dim3(n_slots), dim3(threads), 0, st, scores, seq, n, largest ? 1 : 0, idx);
-  return hipGetLastError();
+  for (long b = 0; b < n_slots; b += kMaxGrid) {
+    hipLaunchKernelGGL(kern, dim3(static_cast<unsigned>(std::min(kMaxGrid, n_slots - b))), dim3(threads), 0, st,
+                       scores + b * seq, seq, n, largest ? 1 : 0, idx + b * n);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace marcache

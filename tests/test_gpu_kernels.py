@@ -556,3 +556,14 @@ def test_select_of_many_sequences(S):
         torch.cuda.synchronize()
         rule = O.select_most_similar if most else O.select_least_similar
         np.testing.assert_array_equal(idx.cpu().numpy(), np.stack([rule(s[b], n) for b in range(slots)]))
+
+
+def test_select_of_more_sequences_than_one_launch_takes():
+    """2^23 sequences and more: a launch of that many workgroups of 512 threads
+    would be of 2^32 threads, which the runtime refuses."""
+    slots, S = (1 << 23) + 3, 257
+    s = torch.rand((slots, S), generator=torch.Generator(device=DEV).manual_seed(7), device=DEV, dtype=torch.float64)
+    idx = torch.full((slots, 1), -1, dtype=torch.int32, device=DEV)
+    B.k_select(s, 1, idx)
+    torch.cuda.synchronize()
+    assert torch.equal(idx[:, 0].long(), s.argmin(1))
