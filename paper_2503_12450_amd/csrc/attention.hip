@@ -16,6 +16,8 @@
 //
 // fp32 path: fp32 MFMAs, 16 queries per workgroup, the keys split over its
 // waves.
+#include <algorithm>
+
 #include "common.h"
 
 namespace marcache {
@@ -299,7 +301,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_bf16_kernel(const bf16_t* __r
 template <int DH>
 __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ Q, const float* __restrict__ Kc,
                                                        const float* __restrict__ Vc, float* __restrict__ O, int H,
-                                                       int seq, int per_slot, float scale_log2) {
+                                                       int seq, int per_slot, float scale_log2, unsigned first) {
   constexpr int WAVES = 4, QB = 16, KB = 16;
   constexpr int DL = DH / 4;    // floats of a row per lane
   constexpr int DT = DH / 16;   // 16-row tiles of O^T
@@ -309,9 +311,10 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int c = lane & 15, g = lane >> 4;
-  const int qblocks = (per_slot + QB - 1) / QB;
-  const int qb = blockIdx.x % qblocks;
-  const int bh = blockIdx.x / qblocks;
+  const unsigned qblocks = (per_slot + QB - 1) / QB;
+  const unsigned block = first + blockIdx.x;
+  const int qb = block % qblocks;
+  const int bh = block / qblocks;
   const int h = bh % H;
   const int b = bh / H;
   const int D = H * DH;
@@ -455,10 +458,15 @@ static hipError_t attn_launch(int dtype, const void* q, const void* k, const voi
   } else {
     const int qblocks = (per_slot + 15) / 16;
     const long grid = static_cast<long>(n_slots) * H * qblocks;
-    hipLaunchKernelGGL(attn_f32_kernel<DH>, dim3(static_cast<unsigned>(grid)), dim3(256), 0, st,
-                       static_cast<const float*>(q), static_cast<const float*>(k),
-                       static_cast<const float*>(v), static_cast<float*>(out), H, seq, per_slot,
-                       scale_log2);
+    if (grid >= 1l << 32) return hipErrorInvalidConfiguration;
+    for (long first = 0; first < grid; first += kMaxGrid) {
+      hipLaunchKernelGGL(attn_f32_kernel<DH>, dim3(static_cast<unsigned>(std::min(kMaxGrid, grid - first))), dim3(256),
+                         0, st, static_cast<const float*>(q), static_cast<const float*>(k),
+                         static_cast<const float*>(v), static_cast<float*>(out), H, seq, per_slot, scale_log2,
+                         static_cast<unsigned>(first));
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   return hipGetLastError();
 }

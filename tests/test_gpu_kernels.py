@@ -567,3 +567,15 @@ def test_select_of_more_sequences_than_one_launch_takes():
     B.k_select(s, 1, idx)
     torch.cuda.synchronize()
     assert torch.equal(idx[:, 0].long(), s.argmin(1))
+
+
+def test_attention_f32_of_more_blocks_than_one_launch_takes():
+    """2^24 heads and more, one query and one key each: 256 threads per head
+    would be a launch of 2^32.  The softmax of one key is 1."""
+    slots, H, dh = (1 << 20) + 1, 16, 16
+    g = torch.Generator(device=DEV).manual_seed(8)
+    q, k, v = (torch.randn((slots, H, 1, dh), generator=g, device=DEV) for _ in range(3))
+    out = torch.empty((slots, H * dh), device=DEV)
+    B.k_attention("f32", q.view(slots, H * dh), k, v, out, slots, H, 1, dh, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(out, v.view(slots, H * dh))
