@@ -177,7 +177,9 @@ struct EpiArgs {
 
 hipError_t launch_gemm(int dtype, const void* A, const void* W, int M, int N, int K,
                        const EpiArgs& epi, hipStream_t st);
-void set_gemm_variant(int v);  // -1: by shape
+// -1: by shape; kFew + a FewTile: that tile (fp32: up to FEW_64x48, refused past it)
+constexpr int kFew = 100;
+void set_gemm_variant(int v);
 
 // The same product for few rows (gemm_few.hip) with tiles of the named size;
 // arguments checked and completed by launch_gemm, which chooses it.

@@ -621,7 +621,7 @@ static hipError_t gemm_launch(const void* A, const void* W, int M, int N, int K,
 
 // Tile choice.  Every configuration uses the same MFMA and visits k in the
 // same order, so the choice never changes a result bit.
-int g_gemm_variant = -1;  // test hook: force a variant (-1 = by shape)
+int g_gemm_variant = -1;  // test hook: force a variant, or a few-row tile as kFew + tile (-1 = by shape)
 
 // Persistent 256 x 256 launches whose last round of tiles would leave CUs
 // idle: the whole rounds keep the 256 x 256 tiles (rows [0, M1)), and the
@@ -680,7 +680,6 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
 //    faster (8192 x 1280 x 5120: 108 us against 126), inside a step, with the
 //    residual in HBM, they are not (86 against 84 us for proj and fc2).
 // Returns kFew + tile for gemm_few.hip, else the variant.
-constexpr int kFew = 100;
 static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
   static const int cus = device_cus();  // of the first device used: only speed depends on it
   const bool resid = kind == EPI_RESIDUAL || kind == EPI_GATE, act = kind == EPI_GELU || kind == EPI_SILU;
@@ -748,10 +747,8 @@ static hipError_t gemm_pick(const void* A, const void* W, int M, int N, int K, c
                             hipStream_t st) {
   const bool by_shape = g_gemm_variant < 0;
   int v = g_gemm_variant;
-  if (by_shape) {
-    v = choose_kernel(sizeof(T) == 2, KIND, M, N, K);
-    if (v >= kFew) return launch_gemm_few(sizeof(T) == 2 ? DT_BF16 : DT_F32, v - kFew, A, W, M, N, K, e, st);
-  }
+  if (by_shape) v = choose_kernel(sizeof(T) == 2, KIND, M, N, K);
+  if (v >= kFew) return launch_gemm_few(sizeof(T) == 2 ? DT_BF16 : DT_F32, v - kFew, A, W, M, N, K, e, st);
   // variants 8..15: the configurations of 0..7 launched persistent
   const bool persist = v >= 8;
   if (persist) v -= 8;

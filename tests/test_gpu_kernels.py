@@ -178,6 +178,109 @@ def test_few_row_products_are_bitwise_the_tiled_ones(dtype, M, N, K):
     _close(_host(got[0])[rows], ref, dtype)
 
 
+FEW_TILES = ["16x16", "32x32", "32x64", "64x48", "64x64", "64x96", "128x64"]
+FEW_F32 = 4  # the tiles that exist for fp32
+
+
+def _few_row_tile(tile):
+    """Forces a few-row tile for every product (None: by shape), which the
+    tuning hook of the C ABI cannot name."""
+    B.load()["_ZN8marcache16set_gemm_variantEi"](-1 if tile is None else 100 + tile)
+
+
+def _awkward(shape, seed, dtype):
+    """Values spread over 2^24, the second half of every row nearly minus the
+    first: sums whose rounding shows in which order they were formed."""
+    g = np.random.Generator(np.random.Philox(seed))
+    a = np.ldexp(g.standard_normal(shape), g.integers(-12, 12, shape)).astype(np.float32)
+    k = shape[1] // 2
+    a[:, k:2 * k] = -a[:, :k] * (1.0 + 0.01 * g.standard_normal((shape[0], k)).astype(np.float32))
+    return to_storage(a, dtype)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("tile", range(len(FEW_TILES)), ids=FEW_TILES)
+def test_every_few_row_tile_is_bitwise_the_tiled_kernel(dtype, tile):
+    """Each tile of the few-row kernel under every epilogue of the per-kernel
+    entry points: rows and columns that end mid-tile, three slots with ragged
+    rows, K from one slice to past the deepest ring, operands of one magnitude
+    and of many."""
+    if dtype == "f32" and tile >= FEW_F32:
+        a = torch.zeros((16, 64), device=DEV)
+        try:
+            _few_row_tile(tile)
+            with pytest.raises(B.MarError):
+                B.k_linear(dtype, a, a, torch.zeros(16, device=DEV), torch.empty((16, 16), device=DEV))
+        finally:
+            _few_row_tile(None)
+        return
+    for n, (slots, per, N, D, dh, awkward) in enumerate([(1, 1, 8, 64, 16, False), (3, 45, 200, 192, 48, True),
+                                                         (3, 70, 328, 320, 80, False), (2, 131, 136, 640, 64, True),
+                                                         (3, 43, 1032, 1152, 32, True)]):
+        M, seq, K = slots * per, per + 7, D
+        a_h = _awkward((M, K), 300 + n, dtype) if awkward else normal_rows((M, K), seed=300 + n, dtype=dtype)
+        a = to_device(a_h, dtype)
+        w = to_device(_awkward((N, K), 310 + n, dtype) if awkward else normal_rows((N, K), seed=310 + n, std=0.05,
+                                                                                   dtype=dtype), dtype)
+        wq = to_device(normal_rows((3 * D, D), seed=320 + n, std=0.05, dtype=dtype), dtype)
+        bias, bq = to_device(normal_rows((N,), seed=330 + n), "f32"), to_device(normal_rows((3 * D,), seed=340 + n), "f32")
+        resid = to_device(normal_rows((M, N), seed=350 + n), "f32")
+        idx = torch.from_numpy(random_index_sets(slots, seq, per, seed=360 + n).reshape(-1)).to(DEV)
+        H = D // dh
+
+        def products():
+            out, act = (torch.full((M, N), 7.0, dtype=a.dtype, device=DEV) for _ in range(2))
+            B.k_linear(dtype, a, w, bias, out)
+            B.k_linear(dtype, a, w, bias, act, gelu=True)
+            h = resid.clone()
+            B.k_linear_residual(dtype, a, w, bias, h, h)
+            y = torch.full((slots * seq, N), 7.0, device=DEV)
+            copy = torch.full((M, N), 7.0, device=DEV)
+            B.k_linear_residual(dtype, a, w, bias, resid, y, out_idx=idx, per_slot=per, seq=seq, resid_copy=copy)
+            outs = [out, act, h, y, copy]
+            for at, S in ((idx, seq), (None, per)):  # scattered and dense rows
+                q = torch.full((M, D), 7.0, dtype=a.dtype, device=DEV)
+                kv = [torch.full((slots, H, S, dh), 7.0, dtype=a.dtype, device=DEV) for _ in range(3)]
+                B.k_qkv(dtype, a, wq, bq, D, H, S, per, q_out=q, k_cache=kv[0], v_cache=kv[1], v_copy=kv[2], idx=at)
+                outs += [q, *kv]
+            torch.cuda.synchronize()
+            return outs
+
+        try:
+            _few_row_tile(tile)
+            got = products()
+            B.k_gemm_variant(4)
+            want = products()
+        finally:
+            B.k_gemm_variant(-1)
+        for g, r in zip(got, want):
+            assert torch.equal(g, r)
+
+
+@pytest.mark.parametrize("tile", range(len(FEW_TILES)), ids=FEW_TILES)
+def test_every_few_row_tile_is_bitwise_the_tiled_kernel_in_the_head(tile):
+    """The SiLU and gated-residual epilogues of every tile, through the
+    diffusion head with all its products forced."""
+    from paper_2503_12450_amd.device import upload_head
+    from paper_2503_12450_amd.workload import HeadDims, head_weights
+    hd = HeadDims(width=448, depth=2, cond_dim=64, token_dim=16, steps=4, train_steps=40, freq_dim=64, max_rows=90)
+    W = upload_head(head_weights(hd, seed=81), hd.dtype)
+    y = to_device(normal_rows((77, hd.cond_dim), seed=82), "f32")
+    idx = torch.arange(77, dtype=torch.int32, device=DEV)
+    x0 = to_device(normal_rows((77, hd.token_dim), seed=83), "f32")
+    xi = to_device(normal_rows((hd.steps, 77, hd.token_dim), seed=84), "f32")
+    out = [torch.empty((77, hd.token_dim), device=DEV) for _ in range(2)]
+    try:
+        _few_row_tile(tile)
+        B.MarHead(hd, W).sample(y, y, idx, idx, x0, xi, 3.0, out[0])
+        B.k_gemm_variant(4)
+        B.MarHead(hd, W).sample(y, y, idx, idx, x0, xi, 3.0, out[1])
+        torch.cuda.synchronize()
+    finally:
+        B.k_gemm_variant(-1)
+    assert torch.equal(*out)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("variant", list(range(8, 16)))
 def test_persistent_workgroups_walk_several_tiles(dtype, variant):
