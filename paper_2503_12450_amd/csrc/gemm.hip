@@ -661,24 +661,29 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
   return gemm_launch<T, 256, 128, 2, 2, 3, 128, KIND>(A2, W, M2, N, K, e2, false, st);
 }
 
-// Which kernel runs a product, by the time each would take: a launch of
-// `tiles` tiles, one per CU at a time, costs its rounds times (a fixed part:
-// first loads, epilogue; plus a part per 128-byte slice of K).  The constants
-// are measured on MI355X (microseconds; fits within about 10 % over M from 10
-// to 40960, N and K from 768 to 5120, 33280 for the head's modulation):
-//  * few-row tiles (gemm_few.hip): at most one per CU; the one-wave 16 x 16
-//    and the 32 x 32 tiles share a CU, whose LDS then bounds them;
-//  * 128 x 128 tiles: at most 256 of them run one per CU with eight waves
-//    (1111 x 3080 x 768: 11.2 us, four waves 11.5), more run two per CU, 2.05 ns per tile and slice, with no
-//    hard rounds (6400 x 1024 x 4096: 61 us, against 82 in 100 tiles of 256 x
-//    256); the head's wide products on few rows persistent;
-//  * 256 x 256 tiles: 1.4 us per slice when every CU has one, 0.9 when few do
+// Which kernel runs a product: the one that would take the least time, by a
+// model of each fitted on MI355X to 5200 products of random sizes (M from 1 to
+// 41000, N from 16 to 8192 and the head's 26624 and 33280, K from 64 to 5120,
+// every kernel on each; microseconds; the choice is within 0.7 % of the fastest
+// in the mean, few-row products within 0.3 %):
+//  * up to two 128 x 128 tiles per CU, every kernel of smaller tiles.  The
+//    fullest CU has n tiles, `resident` of them at a time.  A tile alone pays a
+//    fixed part (first loads, epilogue) and a part per 128-byte slice of K;
+//    tiles that share the CU share its LDS and matrix cores.  Every further
+//    tile and every further round of resident tiles costs a part of its own:
+//    without it short K went to thousands of small tiles (29807 x 128 x 128:
+//    13.9 us in 32 x 32 tiles, 5.2 in 128 x 128; 1593 x 1720 x 320: 11.6, 6.4).
+//  * beyond, 128 x 128 tiles two per CU, with no hard rounds (6400 x 1024 x
+//    4096: 61 us, against 82 in 100 tiles of 256 x 256), or 256 x 256 tiles
 //    (8192 x 3840 x 1280, 480 tiles: 73 us against 85 in 128 x 128 tiles, 80
-//    against 92 inside a cached step); persistent (balanced) from three rounds
-//    on, with GELU or SiLU from five.  The fp32 residual products keep two 128
-//    x 128 tiles per CU up to two rounds: alone 160 tiles of 256 x 256 are
+//    against 92 inside a cached step), persistent and balanced from two full
+//    rounds on, with GELU or SiLU from five; the fp32 residual products keep
+//    128 x 128 up to two rounds of 256 x 256: alone 160 tiles of 256 x 256 are
 //    faster (8192 x 1280 x 5120: 108 us against 126), inside a step, with the
 //    residual in HBM, they are not (86 against 84 us for proj and fc2).
+//    The head's wide products on few rows run persistent.
+//  * fp32 has no few-row tiles past 64 x 48 (its MFMAs bound it there) and
+//    stays with 64 x 64 and 128 x 128 tiles (all others within 2 % of them).
 // Returns kFew + tile for gemm_few.hip, else the variant.
 static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
   static const int cus = device_cus();  // of the first device used: only speed depends on it
@@ -687,6 +692,8 @@ static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
   const float per_cu = 1.0f / cus;
   // (tile sizes are literals below, so that a call costs the host no divisions)
   auto tiles = [&](int bm, int bn) { return static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  auto fullest = [&](long t) { return static_cast<int>(static_cast<float>(t + cus - 1) * per_cu); };
+  auto by_kind = [&](float plain, float a, float r) { return resid ? r : act ? a : plain; };
   int best = 4;
   float cost = 1e30f;
   auto offer = [&](int v, float c) {
@@ -695,50 +702,56 @@ static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
       best = v;
     }
   };
-  // few-row tiles: alone on a CU, or sharing it (`shared`: slice time per tile of the CU)
-  auto alone = [&](FewTile tile, long t, float fixed, float slice) {
-    if (t <= cus) offer(kFew + tile, fixed + s * slice);
-  };
-  auto sharing = [&](FewTile tile, long t, float fixed, float slice, float shared) {
-    offer(kFew + tile, fixed + s * std::max(slice, shared * static_cast<int>((t + cus - 1) * per_cu)));
+  // n tiles on the fullest CU, up to three rounds of `resident`; `tile` and
+  // `round`: what a further one costs; `slice`: of a tile alone, `shared`: per
+  // tile of those that run together
+  auto small = [&](int v, int n, int resident, float fixed, float tile, float round, float slice, float shared) {
+    if (n > 3 * resident) return;
+    const int full = n / resident, rem = n - full * resident;
+    offer(v, fixed + tile * (n - 1) + round * (full + (rem > 0) - 1) +
+                 s * (full * std::max(slice, shared * resident) + (rem > 0 ? std::max(slice, shared * rem) : 0.0f)));
   };
   const long t128 = tiles(128, 128);
-  if (t128 <= 2 * cus) {  // more are never few rows
-    if (bf16) {
-      sharing(FEW_16x16, tiles(16, 16), 2.0f, 0.084f, 0.045f);
-      sharing(FEW_32x32, tiles(32, 32), 2.3f, 0.083f, 0.094f);
-      alone(FEW_32x64, tiles(32, 64), 2.5f, 0.124f);
-      alone(FEW_64x48, tiles(64, 48), 2.9f, 0.149f);
-      alone(FEW_64x64, tiles(64, 64), 2.9f, 0.169f);
-      alone(FEW_64x96, tiles(64, 96), 3.6f, 0.205f);
-      alone(FEW_128x64, tiles(128, 64), 3.8f, 0.254f);
-    } else {
-      sharing(FEW_16x16, tiles(16, 16), 2.2f, 0.245f, 0.069f);
-      sharing(FEW_32x32, tiles(32, 32), 2.6f, 0.255f, 0.22f);
-      alone(FEW_32x64, tiles(32, 64), 3.2f, 0.42f);
-      alone(FEW_64x48, tiles(64, 48), 3.8f, 0.55f);
-    }
-  }
+  const int n128 = fullest(t128), n64 = fullest(tiles(64, 64));
   if (!bf16) {
-    // fp32: the 64 x 64 tiles of the tiled kernel, then its 128 x 128 tiles
-    // (all configurations within 2 % of each other on larger products)
-    offer(6, 2.7f + s * 0.6f * std::max(1.0f, tiles(64, 64) * per_cu));
-    offer(t128 <= cus ? 7 : 4, 6.0f + s * 1.95f * std::max(1.0f, t128 * per_cu));
+    if (n128 <= 2) {
+      small(kFew + FEW_16x16, fullest(tiles(16, 16)), 4, 2.3f + by_kind(0, 0.16f, 0.23f), 0.28f, 0.55f, 0.244f, 0.066f);
+      small(kFew + FEW_32x32, fullest(tiles(32, 32)), 2, 2.53f + by_kind(0, 0.16f, 0.17f), 0.54f, 0.08f, 0.254f, 0.206f);
+      small(kFew + FEW_32x64, fullest(tiles(32, 64)), 1, 2.84f + by_kind(0, 0.25f, 0.17f), 0.0f, 1.95f, 0.434f, 0.0f);
+      small(kFew + FEW_64x48, fullest(tiles(64, 48)), 1, 3.24f + by_kind(0, 0.31f, 0.34f), 0.0f, 2.6f, 0.586f, 0.0f);
+      if (t128 <= cus) offer(7, 4.0f + by_kind(0, 2.1f, 1.6f) + s * 2.02f);
+    }
+    offer(6, 2.7f + by_kind(0, 0.55f, 0.53f) + 0.9f * (n64 - 1) + s * std::max(0.62f, 0.54f * n64));
+    offer(4, 4.3f + by_kind(0, 2.5f, 1.6f) + 2.9f * (n128 - 1) + s * std::max(2.0f, 1.906f * n128));
+    return best;
+  }
+  if (n128 <= 2) {
+    small(kFew + FEW_16x16, fullest(tiles(16, 16)), 4, 2.41f + by_kind(0, 0.08f, 0.18f), 0.14f, by_kind(3.06f, 0.79f, 0.88f),
+          0.062f, 0.031f);
+    small(kFew + FEW_32x32, fullest(tiles(32, 32)), 2, 2.58f + by_kind(0, 0.08f, 0.18f), 0.52f, by_kind(1.56f, 0.11f, 0.36f),
+          0.055f, 0.07f);
+    small(kFew + FEW_32x64, fullest(tiles(32, 64)), 1, 2.76f + by_kind(0, 0.11f, 0.23f), 0.0f, by_kind(4.41f, 1.68f, 2.06f),
+          0.105f, 0.0f);
+    small(kFew + FEW_64x48, fullest(tiles(64, 48)), 1, 2.98f + by_kind(0, 0.14f, 0.36f), 0.0f, by_kind(2.32f, 1.93f, 2.5f),
+          0.149f, 0.0f);
+    small(kFew + FEW_64x64, n64, 2, 2.69f + by_kind(0, 0.15f, 0.44f), 0.83f, by_kind(0.24f, 0.0f, 1.13f), 0.134f, 0.172f);
+    small(kFew + FEW_64x96, fullest(tiles(64, 96)), 1, 2.9f + by_kind(0, 0.29f, 0.46f), 0.0f, by_kind(3.18f, 2.09f, 3.24f),
+          0.229f, 0.0f);
+    small(kFew + FEW_128x64, fullest(tiles(128, 64)), 1, 3.07f + by_kind(0, 0.46f, 0.82f), 0.0f,
+          by_kind(1.92f, 2.62f, 4.26f), 0.276f, 0.0f);
+    small(6, n64, 3, 2.78f + by_kind(0, 0.22f, 0.46f), 0.53f, by_kind(0.0f, 0.49f, 1.4f), 0.216f, 0.19f);
+    small(7, n128, 1, 3.28f + by_kind(0, 1.11f, 1.34f), 0.0f, by_kind(2.0f, 3.05f, 4.7f), 0.474f, 0.0f);
+    small(4, n128, 2, 3.3f + by_kind(0, 1.41f, 1.94f), 2.02f, 0.0f, 0.506f, 0.405f);
     return best;
   }
   const long t256 = tiles(256, 256);
-  if (t128 <= cus) {
-    offer(7, 6.2f + s * 0.46f);
-  } else if (resid) {
-    offer(t256 <= 2 * cus ? 4 : 8, 5.0f + t128 * (s * 2.05e-3f + 0.016f));
-    return best;
-  } else {
-    offer(N >= 8192 && M <= 1024 ? 12 : 4, 5.0f + t128 * (s * 2.05e-3f + (act ? 0.006f : 0.003f)));
-  }
-  if (resid) return best;
+  if (resid) return t256 <= 2 * cus ? 4 : 8;
+  offer(N >= 8192 && M <= 1024 ? 12 : 4, 8.3f + t128 * (s * 1.88e-3f + (act ? 0.0119f : 0.0039f)));
   const long full = t256 / cus, last = t256 - full * cus;
-  auto round256 = [&](long t) { return (act ? 13.0f : 7.0f) + s * (0.85f + 0.55f * t * per_cu); };
-  offer(full >= (act ? 5 : 2) ? 8 : 0, full * round256(cus) + (last > 0 ? round256(last) : 0.0f));
+  const bool persist = full >= (act ? 5 : 2);
+  const float round = persist ? (act ? 12.4f : 5.7f) : (act ? 17.5f : 8.9f);
+  auto round256 = [&](long t) { return round + s * (0.58f + 0.85f * t * per_cu); };
+  offer(persist ? 8 : 0, (persist ? 9.7f : 0.0f) + full * round256(cus) + (last > 0 ? round256(last) : 0.0f));
   return best;
 }
 
