@@ -685,9 +685,10 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
 //  * fp32 has no few-row tiles past 64 x 48 (its MFMAs bound it there) and
 //    stays with 64 x 64 and 128 x 128 tiles (all others within 2 % of them).
 // Returns kFew + tile for gemm_few.hip, else the variant.
-static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
+template <bool bf16, int KIND>
+static int choose_kernel(int M, int N, int K) {
   static const int cus = device_cus();  // of the first device used: only speed depends on it
-  const bool resid = kind == EPI_RESIDUAL || kind == EPI_GATE, act = kind == EPI_GELU || kind == EPI_SILU;
+  constexpr bool resid = KIND == EPI_RESIDUAL || KIND == EPI_GATE, act = KIND == EPI_GELU || KIND == EPI_SILU;
   const float s = static_cast<float>(K) * (bf16 ? 2 : 4) / 128;
   const float per_cu = 1.0f / cus;
   // (tile sizes are literals below, so that a call costs the host no divisions)
@@ -711,11 +712,16 @@ static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
     offer(v, fixed + tile * (n - 1) + round * (full + (rem > 0) - 1) +
                  s * (full * std::max(slice, shared * resident) + (rem > 0 ? std::max(slice, shared * rem) : 0.0f)));
   };
+  // Which kernels can win at all depends on how many 16 x 16 tiles there are;
+  // the others are not looked at, which the smallest calls, bound by the host,
+  // would feel (45 ns per launch for all of them).
   const long t128 = tiles(128, 128);
+  const int n16 = fullest(tiles(16, 16));
+  if (n16 <= (bf16 ? 2 : 1)) return kFew + FEW_16x16;
   const int n128 = fullest(t128), n64 = fullest(tiles(64, 64));
-  if (!bf16) {
+  if constexpr (!bf16) {
     if (n128 <= 2) {
-      small(kFew + FEW_16x16, fullest(tiles(16, 16)), 4, 2.3f + by_kind(0, 0.16f, 0.23f), 0.28f, 0.55f, 0.244f, 0.066f);
+      small(kFew + FEW_16x16, n16, 4, 2.3f + by_kind(0, 0.16f, 0.23f), 0.28f, 0.55f, 0.244f, 0.066f);
       small(kFew + FEW_32x32, fullest(tiles(32, 32)), 2, 2.53f + by_kind(0, 0.16f, 0.17f), 0.54f, 0.08f, 0.254f, 0.206f);
       small(kFew + FEW_32x64, fullest(tiles(32, 64)), 1, 2.84f + by_kind(0, 0.25f, 0.17f), 0.0f, 1.95f, 0.434f, 0.0f);
       small(kFew + FEW_64x48, fullest(tiles(64, 48)), 1, 3.24f + by_kind(0, 0.31f, 0.34f), 0.0f, 2.6f, 0.586f, 0.0f);
@@ -726,20 +732,26 @@ static int choose_kernel(bool bf16, int kind, int M, int N, int K) {
     return best;
   }
   if (n128 <= 2) {
-    small(kFew + FEW_16x16, fullest(tiles(16, 16)), 4, 2.41f + by_kind(0, 0.08f, 0.18f), 0.14f, by_kind(3.06f, 0.79f, 0.88f),
-          0.062f, 0.031f);
-    small(kFew + FEW_32x32, fullest(tiles(32, 32)), 2, 2.58f + by_kind(0, 0.08f, 0.18f), 0.52f, by_kind(1.56f, 0.11f, 0.36f),
-          0.055f, 0.07f);
-    small(kFew + FEW_32x64, fullest(tiles(32, 64)), 1, 2.76f + by_kind(0, 0.11f, 0.23f), 0.0f, by_kind(4.41f, 1.68f, 2.06f),
-          0.105f, 0.0f);
-    small(kFew + FEW_64x48, fullest(tiles(64, 48)), 1, 2.98f + by_kind(0, 0.14f, 0.36f), 0.0f, by_kind(2.32f, 1.93f, 2.5f),
-          0.149f, 0.0f);
-    small(kFew + FEW_64x64, n64, 2, 2.69f + by_kind(0, 0.15f, 0.44f), 0.83f, by_kind(0.24f, 0.0f, 1.13f), 0.134f, 0.172f);
+    if (n16 <= 24) {
+      small(kFew + FEW_16x16, n16, 4, 2.41f + by_kind(0, 0.08f, 0.18f), 0.14f, by_kind(3.06f, 0.79f, 0.88f), 0.062f, 0.031f);
+      small(kFew + FEW_32x32, fullest(tiles(32, 32)), 2, 2.58f + by_kind(0, 0.08f, 0.18f), 0.52f,
+            by_kind(1.56f, 0.11f, 0.36f), 0.055f, 0.07f);
+    }
+    if (n16 <= 3) return best;
+    if (n16 <= 20)
+      small(kFew + FEW_32x64, fullest(tiles(32, 64)), 1, 2.76f + by_kind(0, 0.11f, 0.23f), 0.0f,
+            by_kind(4.41f, 1.68f, 2.06f), 0.105f, 0.0f);
+    if (n16 <= 32)
+      small(kFew + FEW_64x48, fullest(tiles(64, 48)), 1, 2.98f + by_kind(0, 0.14f, 0.36f), 0.0f,
+            by_kind(2.32f, 1.93f, 2.5f), 0.149f, 0.0f);
+    small(kFew + FEW_64x64, n64, 2, 2.69f + by_kind(0, 0.15f, 0.44f), 0.83f, by_kind(0.24f, 0.0f, 1.13f), 0.134f, 0.174f);
+    if (n16 <= 4) return best;
     small(kFew + FEW_64x96, fullest(tiles(64, 96)), 1, 2.9f + by_kind(0, 0.29f, 0.46f), 0.0f, by_kind(3.18f, 2.09f, 3.24f),
           0.229f, 0.0f);
     small(kFew + FEW_128x64, fullest(tiles(128, 64)), 1, 3.07f + by_kind(0, 0.46f, 0.82f), 0.0f,
           by_kind(1.92f, 2.62f, 4.26f), 0.276f, 0.0f);
     small(6, n64, 3, 2.78f + by_kind(0, 0.22f, 0.46f), 0.53f, by_kind(0.0f, 0.49f, 1.4f), 0.216f, 0.19f);
+    if (n16 <= 20) return best;
     small(7, n128, 1, 3.28f + by_kind(0, 1.11f, 1.34f), 0.0f, by_kind(2.0f, 3.05f, 4.7f), 0.474f, 0.0f);
     small(4, n128, 2, 3.3f + by_kind(0, 1.41f, 1.94f), 2.02f, 0.0f, 0.506f, 0.405f);
     return best;
@@ -760,7 +772,7 @@ static hipError_t gemm_pick(const void* A, const void* W, int M, int N, int K, c
                             hipStream_t st) {
   const bool by_shape = g_gemm_variant < 0;
   int v = g_gemm_variant;
-  if (by_shape) v = choose_kernel(sizeof(T) == 2, KIND, M, N, K);
+  if (by_shape) v = choose_kernel<sizeof(T) == 2, KIND>(M, N, K);
   if (v >= kFew) return launch_gemm_few(sizeof(T) == 2 ? DT_BF16 : DT_F32, v - kFew, A, W, M, N, K, e, st);
   // variants 8..15: the configurations of 0..7 launched persistent
   const bool persist = v >= 8;

@@ -682,3 +682,40 @@ def test_attention_f32_of_more_blocks_than_one_launch_takes():
     B.k_attention("f32", q.view(slots, H * dh), k, v, out, slots, H, 1, dh, 1)
     torch.cuda.synchronize()
     assert torch.equal(out, v.view(slots, H * dh))
+
+
+@pytest.mark.parametrize("dtype,M,N,K", [("bf16", 29807, 128, 128), ("bf16", 1268, 4424, 64), ("bf16", 1593, 1720, 320),
+                                         ("bf16", 554, 6016, 128), ("bf16", 11558, 416, 128), ("bf16", 6, 2440, 1024),
+                                         ("bf16", 1111, 3080, 768), ("f32", 1626, 448, 64), ("f32", 74, 7080, 128)])
+def test_product_choice_is_near_the_fastest(dtype, M, N, K):
+    """The kernel chosen by shape against every other one, in launches of a
+    captured graph (no host time): products of a short K once took three times
+    the fastest in thousands of small tiles.  The bound leaves room for the
+    spread of timings of a few microseconds."""
+    a = to_device(normal_rows((M, K), seed=201, dtype=dtype), dtype)
+    w = to_device(normal_rows((N, K), seed=202, std=0.05, dtype=dtype), dtype)
+    bias = to_device(normal_rows((N,), seed=203), "f32")
+    out = torch.empty((M, N), dtype=a.dtype, device=DEV)
+    few = range(FEW_F32 if dtype == "f32" else len(FEW_TILES))
+    graphs = {}
+    try:
+        for v in (-1, 0, 4, 6, 7, *(100 + t for t in few)):
+            _few_row_tile(None) if v < 0 else _few_row_tile(v - 100)
+            B.k_linear(dtype, a, w, bias, out)
+            torch.cuda.synchronize()
+            graphs[v] = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graphs[v]):
+                for _ in range(20):
+                    B.k_linear(dtype, a, w, bias, out)
+    finally:
+        _few_row_tile(None)
+    t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    us = {}
+    for _ in range(4):
+        for v, g in graphs.items():
+            t0.record()
+            g.replay()
+            t1.record()
+            t1.synchronize()
+            us[v] = min(us.get(v, 1e9), t0.elapsed_time(t1) * 1e3 / 20)
+    assert us[-1] <= 1.35 * min(us.values()), us
