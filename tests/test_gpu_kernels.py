@@ -106,6 +106,28 @@ def test_gelu_over_wide_range(dtype):
     np.testing.assert_allclose(_host(out), want, **tol)
 
 
+@pytest.mark.parametrize("variant", [-1, 4])  # the few-row kernel and the tiled one
+def test_gelu_negative_tail(variant):
+    """bf16 GELU for pre-activations from -6 to 0, where the result is far
+    smaller than its argument: the approximation's absolute error of 2.4e-4
+    |x| (evaluated over the formula; 2.5e-4 here for its fp32 arithmetic) and
+    half a bf16 step of the result."""
+    M, N, K = 48, 2048, 64
+    bias = np.linspace(-6, 0, N, dtype=np.float32)
+    out = torch.empty((M, N), dtype=torch.bfloat16, device=DEV)
+    try:
+        B.k_gemm_variant(variant)
+        B.k_linear("bf16", torch.zeros((M, K), dtype=torch.bfloat16, device=DEV),
+                   torch.zeros((N, K), dtype=torch.bfloat16, device=DEV), to_device(bias, "f32"), out, gelu=True)
+    finally:
+        B.k_gemm_variant(-1)
+    torch.cuda.synchronize()
+    want = np.broadcast_to(O.gelu(bias.astype(np.float64)), (M, N))
+    bound = 2.5e-4 * np.abs(bias.astype(np.float64))
+    bound = bound + 2.0 ** -8 * (np.abs(want) + bound) + 1e-12
+    assert np.all(np.abs(_host(out) - want) <= bound)
+
+
 @pytest.mark.parametrize("variant", list(range(16)))
 def test_tile_variants_are_bitwise_identical(variant):
     """Every tile configuration visits k in the same order: same bits."""
@@ -595,6 +617,30 @@ def test_scores_bitwise_over_magnitudes(slots, H, dh):
     ends = [0, slots - 1]
     np.testing.assert_array_equal(scores.cpu().numpy()[ends], O.cosine_scores(v[ends], r[ends]))
     assert torch.equal(dr, dv)
+
+
+@pytest.mark.parametrize("slots", [2, 450])  # one wave per token; runs of tokens per wave
+@pytest.mark.parametrize("H,dh", [(16, 64), (5, 48), (16, 80), (2, 128), (3, 8)])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_scores_bitwise_without_update(dtype, slots, H, dh):
+    """Both kernels in both types over chunks per row that are no power of two
+    and leave lanes over (fp32 48: 12 chunks, 80: 20), rows of many magnitudes
+    among them; without update_ref the reference stays as it was."""
+    S, D = 25, H * dh
+    g = np.random.Generator(np.random.Philox(78))
+    v, r = (g.standard_normal((slots, S, D)).astype(np.float32) for _ in range(2))
+    for s in (0, slots - 1):
+        v[s, ::3] = np.ldexp(v[s, ::3], g.integers(-30, 30, v[s, ::3].shape))
+        r[s, ::4] = np.ldexp(r[s, ::4], g.integers(-30, 30, r[s, ::4].shape))
+    v, r = to_storage(v, dtype), to_storage(r, dtype)
+    dv, dr = (to_device(_cache_layout(a, H), dtype) for a in (v, r))
+    before = dr.clone()
+    scores = torch.empty((slots, S), dtype=torch.float64, device=DEV)
+    B.k_scores(dtype, dv, dr, scores)
+    torch.cuda.synchronize()
+    ends = [0, slots - 1]
+    np.testing.assert_array_equal(scores.cpu().numpy()[ends], O.cosine_scores(v[ends], r[ends]))
+    assert torch.equal(dr, before)
 
 
 @pytest.mark.parametrize("slots,S,n", [(4, 320, 50), (2, 320, 0), (2, 320, 320), (1, 1, 1), (3, 1088, 218),
