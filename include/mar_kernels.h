@@ -108,8 +108,9 @@ mar_status mar_k_select_most_similar(const double* scores, int32_t n_slots, int3
 
 /* Tuning hook: force tile configuration `variant` (0 .. MAR_GEMM_VARIANTS-1)
  * for every later matrix product of the process, or -1 to restore the
- * choice by shape.  Every configuration uses the same MFMA instruction and
- * visits k in the same order, so results do not change by a single bit.
+ * choice by shape (which also knows the tiles for few rows, not named here).
+ * Every configuration sums the k of an output in the same order, so results
+ * do not change by a single bit.
  * Not thread-safe with concurrent launches. */
 #define MAR_GEMM_VARIANTS 16
 mar_status mar_k_gemm_variant(int32_t variant);

@@ -619,8 +619,9 @@ static hipError_t gemm_launch(const void* A, const void* W, int M, int N, int K,
                  : gemm_launch_as<T, BM, BN, WAVES_M, WAVES_N, STAGES, ROWB, KIND, false>(A, W, M, N, K, e, st);
 }
 
-// Tile choice.  Every configuration uses the same MFMA and visits k in the
-// same order, so the choice never changes a result bit.
+// Tile choice.  Every configuration sums the k of an output in the same order
+// (the few-row kernel's 16-row MFMAs included), so the choice never changes a
+// result bit.
 int g_gemm_variant = -1;  // test hook: force a variant, or a few-row tile as kFew + tile (-1 = by shape)
 
 // Persistent 256 x 256 launches whose last round of tiles would leave CUs
