@@ -665,8 +665,10 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
 // Which kernel runs a product: the one that would take the least time, by a
 // model of each fitted on MI355X to 5200 products of random sizes (M from 1 to
 // 41000, N from 16 to 8192 and the head's 26624 and 33280, K from 64 to 5120,
-// every kernel on each; microseconds; the choice is within 0.7 % of the fastest
-// in the mean, few-row products within 0.3 %):
+// every kernel on each; microseconds) with weights and activations resident, and
+// corrected on as many whose operands come from HBM, as in a step: the choice is
+// there within 0.2 % of the fastest in the mean up to two 128 x 128 tiles per
+// CU and within 1.4 % beyond:
 //  * up to two 128 x 128 tiles per CU, every kernel of smaller tiles.  The
 //    fullest CU has n tiles, `resident` of them at a time.  A tile alone pays a
 //    fixed part (first loads, epilogue) and a part per 128-byte slice of K;
@@ -674,11 +676,18 @@ static hipError_t gemm_balanced(const void* A, const void* W, int M, int N, int 
 //    tile and every further round of resident tiles costs a part of its own:
 //    without it short K went to thousands of small tiles (29807 x 128 x 128:
 //    13.9 us in 32 x 32 tiles, 5.2 in 128 x 128; 1593 x 1720 x 320: 11.6, 6.4).
+//    From HBM the few-row tiles of 64 x 64 and 128 x 64 lose to the tiled
+//    kernel's 64 x 64, three to a CU, where a CU has two of them and K is short
+//    (2560 x 768 x 768 residual: 10.2 us in 128 x 64, 9.6; 770 x 2304 x 768 qkv:
+//    9.5, 8.7), and two rounds of 64 x 96 to 128 x 128 (4352 x 1024 x 4096: 59.0
+//    us against 53.5).
 //  * beyond, 128 x 128 tiles two per CU, with no hard rounds (6400 x 1024 x
 //    4096: 61 us, against 82 in 100 tiles of 256 x 256), or 256 x 256 tiles
 //    (8192 x 3840 x 1280, 480 tiles: 73 us against 85 in 128 x 128 tiles, 80
 //    against 92 inside a cached step), persistent and balanced from two full
-//    rounds on, with GELU or SiLU from five; the fp32 residual products keep
+//    rounds on (operands from HBM: 24320 x 3072 x 768 with GELU 147 us in
+//    128 x 128 tiles, 140 in 256 x 256, 132 persistent; 36552 x 1096 x 320: 54,
+//    50, 45); the fp32 residual products keep
 //    128 x 128 up to two rounds of 256 x 256: alone 160 tiles of 256 x 256 are
 //    faster (8192 x 1280 x 5120: 108 us against 126), inside a step, with the
 //    residual in HBM, they are not (86 against 84 us for proj and fc2).
@@ -690,6 +699,7 @@ template <bool bf16, int KIND>
 static int choose_kernel(int M, int N, int K) {
   static const int cus = device_cus();  // of the first device used: only speed depends on it
   constexpr bool resid = KIND == EPI_RESIDUAL || KIND == EPI_GATE, act = KIND == EPI_GELU || KIND == EPI_SILU;
+  constexpr float qkv = KIND == EPI_QKV ? 1.0f : 0.0f;
   const float s = static_cast<float>(K) * (bf16 ? 2 : 4) / 128;
   const float per_cu = 1.0f / cus;
   // (tile sizes are literals below, so that a call costs the host no divisions)
@@ -745,13 +755,19 @@ static int choose_kernel(int M, int N, int K) {
     if (n16 <= 32)
       small(kFew + FEW_64x48, fullest(tiles(64, 48)), 1, 2.98f + by_kind(0, 0.14f, 0.36f), 0.0f,
             by_kind(2.32f, 1.93f, 2.5f), 0.149f, 0.0f);
-    small(kFew + FEW_64x64, n64, 2, 2.69f + by_kind(0, 0.15f, 0.44f), 0.83f, by_kind(0.24f, 0.0f, 1.13f), 0.134f, 0.174f);
+    // (the waits of the larger few-row tiles show in a K of 320 to 1024)
+    const bool exposed = !act && n64 >= 2 && M >= 128 && s > 4 && s <= 16;
+    if (!exposed)
+      small(kFew + FEW_64x64, n64, 2, 2.69f + 0.7f * qkv + by_kind(0, 0.15f, 0.44f), 0.83f,
+            by_kind(0.24f, 0.0f, 1.13f), 0.134f, 0.174f);
     if (n16 <= 4) return best;
-    small(kFew + FEW_64x96, fullest(tiles(64, 96)), 1, 2.9f + by_kind(0, 0.29f, 0.46f), 0.0f, by_kind(3.18f, 2.09f, 3.24f),
-          0.229f, 0.0f);
-    small(kFew + FEW_128x64, fullest(tiles(128, 64)), 1, 3.07f + by_kind(0, 0.46f, 0.82f), 0.0f,
-          by_kind(1.92f, 2.62f, 4.26f), 0.276f, 0.0f);
-    small(6, n64, 3, 2.78f + by_kind(0, 0.22f, 0.46f), 0.53f, by_kind(0.0f, 0.49f, 1.4f), 0.216f, 0.19f);
+    if (fullest(tiles(64, 96)) == 1)
+      offer(kFew + FEW_64x96, 2.9f + 0.4f * qkv + by_kind(0, 0.29f, 0.46f) + s * 0.229f);
+    if (!exposed)
+      small(kFew + FEW_128x64, fullest(tiles(128, 64)), 1, 3.07f + 1.5f * qkv + by_kind(0, 0.46f, 0.82f), 0.0f,
+            by_kind(1.92f, 2.62f, 4.26f), 0.276f, 0.0f);
+    small(6, n64, 3, 2.78f + by_kind(0, 0.22f, s < 2 ? 0.46f : 0.3f), 0.53f, by_kind(0.0f, 0.49f, 1.4f), 0.216f,
+          0.19f);
     if (n16 <= 20) return best;
     small(7, n128, 1, 3.28f + by_kind(0, 1.11f, 1.34f), 0.0f, by_kind(2.0f, 3.05f, 4.7f), 0.474f, 0.0f);
     small(4, n128, 2, 3.3f + by_kind(0, 1.41f, 1.94f), 2.02f, 0.0f, 0.506f, 0.405f);
@@ -759,12 +775,12 @@ static int choose_kernel(int M, int N, int K) {
   }
   const long t256 = tiles(256, 256);
   if (resid) return t256 <= 2 * cus ? 4 : 8;
-  offer(N >= 8192 && M <= 1024 ? 12 : 4, 8.3f + t128 * (s * 1.88e-3f + (act ? 0.0119f : 0.0039f)));
+  offer(N >= 8192 && M <= 1024 ? 12 : 4, 8.6f + t128 * (s * 1.88e-3f + (act ? 0.0139f : 0.0039f)));
   const long full = t256 / cus, last = t256 - full * cus;
-  const bool persist = full >= (act ? 5 : 2);
-  const float round = persist ? (act ? 12.4f : 5.7f) : (act ? 17.5f : 8.9f);
-  auto round256 = [&](long t) { return round + s * (0.58f + 0.85f * t * per_cu); };
-  offer(persist ? 8 : 0, (persist ? 9.7f : 0.0f) + full * round256(cus) + (last > 0 ? round256(last) : 0.0f));
+  const bool persist = full >= 2 && s >= 2;
+  const float round = persist ? (act ? 12.6f : 3.45f) : (act ? 18.0f : 8.6f);
+  auto round256 = [&](long t) { return round + s * (0.63f + 0.875f * t * per_cu); };
+  offer(persist ? 8 : 0, (persist ? 10.7f : 0.0f) + full * round256(cus) + (last > 0 ? round256(last) : 0.0f));
   return best;
 }
 
