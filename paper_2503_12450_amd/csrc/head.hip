@@ -267,7 +267,7 @@ __global__ __launch_bounds__(256) void head_lnmod_kernel(const float* __restrict
 // components; the weights of both products are loaded ahead of the reductions.
 // As three kernels (one wave per row and 16 components; the prologue of the
 // next step; the first ln-modulation) it took 12.6 + 8.7 + 3.6 us at 256 tokens
-// of width 1280 on MI355X.  Whole calls of ten sampling steps and two blocks,
+// of width 1280 on MI355X, as one 9.6.  Whole calls of ten sampling steps and two blocks,
 // as three kernels and as this one: 5 tokens of width 1024 485 and 227 us, 64
 // tokens of width 1024 and 64 components 1364 and 354 us, 256 tokens of width
 // 1280 816 and 578 us.
